@@ -264,7 +264,7 @@ pr_status pr_verifier_head(const float* X, int64_t n_rows, const int32_t* offset
   a.max_len = max_len;
   a.weights = weights;
   a.scores = scores;
-  a.ws = static_cast<float*>(workspace);
+  a.ws = workspace;
   return hip_status(launch_head(a, as_stream(stream)));
 }
 

@@ -140,3 +140,44 @@ def test_work_list_edges():
     assert_floats("head score (one long request)", got, ref)
     again = run_head(X, off, weights, max_len=1500)
     assert np.array_equal(got.view(np.uint32), again.view(np.uint32))
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("first", [1, 2, 4, 13, 16, 33])
+def test_neighbours_share_row_groups(first, bad):
+    """Requests that start and end inside the 16-row groups in which queries,
+    keys and values are stored, and 1, 2 and more key tiles long, with an
+    undefined request between them: its score alone is NaN, and the others
+    are what the oracle gives for them. The workspace is exactly as long as
+    asked for, and nothing past it is written."""
+    lengths = [first, 3, 15, 17, 63, 1, 64, 66, 127, 130, 5]
+    X, off = synthetic_sequence(lengths, 31)
+    weights = wl.head_weights(seed=31)
+    broken = [1, 6, 9]
+    Xb = X.copy()
+    for i in broken:
+        Xb[off[i]:off[i + 1], 0] = bad
+    Xd, offd = torch.tensor(Xb, device="cuda"), torch.tensor(off, device="cuda")
+    need = int(pr._abi.lib().pr_verifier_head_workspace(X.shape[0]))
+    buf = torch.full((need + 4096,), 0x7F, dtype=torch.uint8, device="cuda")  # NaN patterns where nothing is written
+    print(f"case head neighbours first={first} bad={bad} rows={X.shape[0]}", flush=True)
+    got = pr.verifier_head(Xd, offd, torch.tensor(weights, device="cuda"), max_len=130, workspace=buf[:need])
+    torch.cuda.synchronize()
+    got = got.cpu().numpy()
+    ref = ohead.head_scores(X.astype(np.float64), off, weights.astype(np.float64))
+    ref[broken] = np.nan
+    assert_floats("head score", got, ref)
+    assert bool((buf[need:] == 0x7F).all())
+
+
+def test_scaled_weights():
+    """Scores of large magnitude: the softmax reference moves at nearly every
+    key tile, and most masses underflow."""
+    lengths = [40, 200, 333]
+    X, off = synthetic_sequence(lengths, 41)
+    weights = wl.head_weights(seed=41)
+    at = 320  # the first layer's query and key rows
+    weights[at:at + 128 * 64] *= 12.0
+    got = run_head(X, off, weights, max_len=333)
+    ref = ohead.head_scores(X.astype(np.float64), off, weights.astype(np.float64))
+    assert_floats("head score (sharp attention)", got, ref)
