@@ -47,17 +47,6 @@ struct CalShared {
   uint32_t sel[2];
 };
 
-__device__ __forceinline__ uint32_t wave_min_u(uint32_t v) {
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) v = min(v, static_cast<uint32_t>(__shfl_xor(v, o)));
-  return v;
-}
-__device__ __forceinline__ uint32_t wave_max_u(uint32_t v) {
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) v = max(v, static_cast<uint32_t>(__shfl_xor(v, o)));
-  return v;
-}
-
 // Adds one to the digit's bin; a wave whose active lanes all share one digit
 // adds once.
 __device__ __forceinline__ void hist_add(uint32_t* h, uint32_t digit) {
@@ -153,12 +142,7 @@ __device__ Select select_step(Select s, uint32_t h0, uint32_t h1, CalShared& sh,
   const int lane = t % kWave;
   const int shift = s.pos - digit_width(s.pos);
   const uint32_t c = h0 + h1;
-  uint32_t incl = c;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint32_t u = __shfl_up(incl, o);
-    if (lane >= o) incl += u;
-  }
+  uint32_t incl = wave_incl_scan_u(c);
   if (lane == kWave - 1) sh.wcnt[w] = incl;
   __syncthreads();
   uint32_t off = 0;

@@ -175,6 +175,55 @@ __device__ __forceinline__ uint32_t wave_sum_u(uint32_t v) {
   return lane63(v);
 }
 
+// Inclusive prefix sum over the lanes of a wave: shifts within the rows of 16
+// lanes, then the row broadcasts carry the rows' totals on. All 64 lanes
+// must be active.
+__device__ __forceinline__ uint32_t wave_incl_scan_u(uint32_t v) {
+  using namespace dpp;
+  v += mov<0x111, 0xf>(0u, v);  // row_shr:1
+  v += mov<0x112, 0xf>(0u, v);  // row_shr:2
+  v += mov<0x114, 0xf>(0u, v);  // row_shr:4
+  v += mov<0x118, 0xf>(0u, v);  // row_shr:8
+  v += mov<kBcast15, 0xa>(0u, v);
+  v += mov<kBcast31, 0xc>(0u, v);
+  return v;
+}
+
+__device__ __forceinline__ uint32_t wave_max_u(uint32_t v) {
+  using namespace dpp;
+  v = max(v, mov<kXor1, 0xf>(0u, v));
+  v = max(v, mov<kXor2, 0xf>(0u, v));
+  v = max(v, mov<kHalfMirror, 0xf>(0u, v));
+  v = max(v, mov<kMirror, 0xf>(0u, v));
+  v = max(v, mov<kBcast15, 0xa>(0u, v));
+  v = max(v, mov<kBcast31, 0xc>(0u, v));
+  return lane63(v);
+}
+__device__ __forceinline__ uint32_t wave_min_u(uint32_t v) { return ~wave_max_u(~v); }
+
+// LDS written by some lanes of a wave is read by others of the same wave:
+// its LDS operations are carried out in order, so only the compiler must be
+// kept from reordering them.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The j-th smallest (1-based) of the n <= 64 keys of a wave's first n lanes:
+// each is counted against all others (as wave-uniform values), ties by lane;
+// the one with j - 1 before it is the answer (0 when there is none).
+__device__ __forceinline__ uint32_t count_select(uint32_t k, int n, uint32_t j) {
+  const int lane = static_cast<int>(__lane_id());
+  uint32_t before = 0;
+  for (int l = 0; l < n; ++l) {
+    const uint32_t o = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(k), l));
+    before += (o < k || (o == k && l < lane)) ? 1u : 0u;
+  }
+  const uint64_t who = __ballot(lane < n && before + 1 == j);
+  return who ? static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(k), static_cast<int>(__builtin_ctzll(who))))
+             : 0u;
+}
+
 // (t1, t1i, t2) merge: larger value first, equal values by lower index; the
 // second value is the larger of the loser's top-1 and both top-2 values.
 __device__ __forceinline__ void top2_merge(float& t1, int32_t& t1i, float& t2, float o1, int32_t o1i, float o2) {

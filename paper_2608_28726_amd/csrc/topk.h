@@ -112,16 +112,6 @@ struct Store {
   }
 };
 
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-  const int lane = __lane_id();
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint32_t t = __shfl_up(v, o);
-    if (lane >= o) v += t;
-  }
-  return v;
-}
-
 // The j-th largest (1-based) of the keys that the threads of the workgroup
 // pass to `keys` (each thread calls keys(fn) and fn(key) for each of its
 // keys; zero keys are ignored). Radix select over 8-bit digits, most
@@ -151,7 +141,7 @@ __device__ uint32_t select_desc(Keys&& keys, uint32_t j, const Lds& s, uint32_t*
       const int l = threadIdx.x;
       const uint32_t c0 = h[255 - 4 * l], c1 = h[254 - 4 * l], c2 = h[253 - 4 * l], c3 = h[252 - 4 * l];
       const uint32_t tot = c0 + c1 + c2 + c3;
-      const uint32_t incl = wave_incl_scan(tot);
+      const uint32_t incl = wave_incl_scan_u(tot);
       const uint32_t excl = incl - tot;
       if (pass == 0 && l == kWave - 1) s.misc[kTotal] = incl;
       if (need > excl && need <= incl) {

@@ -70,6 +70,26 @@ def test_aggregate_synthetic(q):
     _check_agg(g, o, oagg.score_from_aggregates(o))
 
 
+@pytest.mark.parametrize("q", [0.0, 0.25, 1.0])
+def test_aggregate_select_edges(q):
+    """Lengths around one key per lane (counted) and the registers' 1,024
+    keys, with every value tied, tied in part and signed zeros and
+    infinities among them."""
+    rng = np.random.default_rng(77)
+    lengths = [1, 2, 63, 64, 65, 128, 129, 1023, 1024, 1025, 64, 64]
+    offsets = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    f = _synthetic_features(lengths, rng, with_specials=False)
+    n = int(offsets[-1])
+    f["maxprob"] = np.round(f["maxprob"] * 4).astype(np.float32) / 4
+    f["logprob"][rng.integers(0, n, n // 8)] = -np.inf
+    f["margin"][offsets[10]:offsets[11]] = 1.5
+    f["margin"][offsets[11]::2] = -0.0
+    f["margin"][offsets[11] + 1::2] = 0.0
+    g = _gpu_agg(_to_gpu_feats(f), offsets, q=q)
+    o = oagg.request_aggregate({k: v.astype(np.float64) for k, v in f.items()}, offsets, q=q)
+    _check_agg(g, o, oagg.score_from_aggregates(o))
+
+
 def test_score_heads():
     rng = np.random.default_rng(9)
     lengths = rng.integers(1, 300, 30)
