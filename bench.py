@@ -335,7 +335,7 @@ def run_offline(args, torch, pr, wl, w):
     drawn = [torch.empty(b.n_rows, dtype=torch.int32, device="cuda") for b in batches] if sample else None
     if pipeline:
         head_w = torch.tensor(wl.head_weights(), device="cuda")
-        head_ws = [torch.empty(max(int(pr._abi.lib().pr_verifier_head_workspace(b.n_rows)), 1), dtype=torch.uint8,
+        head_ws = [torch.empty(max(int(pr._abi.lib().pr_verifier_head_workspace_full(b.n_rows)), 1), dtype=torch.uint8,
                                device="cuda") for b in batches]
         head_ev = []
     if sequence:

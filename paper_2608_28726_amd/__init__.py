@@ -241,7 +241,9 @@ def verifier_head(X: torch.Tensor, offsets: torch.Tensor, weights: torch.Tensor,
     (``pr_verifier_head``). ``X`` float32 [n_rows, 4] (as returned by
     :func:`feature_sequence`), ``offsets`` int32 [n_req + 1], ``weights``
     float32 [67,329] in the documented layout. ``max_len``: at least the
-    longest request's length (default: n_rows). Returns float32 [n_req]."""
+    longest request's length (default: n_rows). ``workspace``: optional device
+    scratch of ``pr_verifier_head_workspace_full(n_rows)`` bytes (or, at half
+    the speed, ``pr_verifier_head_workspace(n_rows)``). Returns float32 [n_req]."""
     if X.dtype != torch.float32 or not X.is_cuda or X.dim() != 2 or X.shape[1] != 4 or not X.is_contiguous():
         raise ValueError("X must be a contiguous float32 [n_rows, 4] CUDA tensor")
     if offsets.dtype != torch.int32 or not offsets.is_cuda or offsets.dim() != 1 or not offsets.is_contiguous():
@@ -253,9 +255,8 @@ def verifier_head(X: torch.Tensor, offsets: torch.Tensor, weights: torch.Tensor,
     n_req = offsets.shape[0] - 1
     _check_workspace(workspace, X.device)
     L = _abi.lib()
-    need = int(L.pr_verifier_head_workspace(n))
-    if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = torch.empty(need, dtype=torch.uint8, device=X.device)
+    if workspace is None or workspace.numel() * workspace.element_size() < int(L.pr_verifier_head_workspace(n)):
+        workspace = torch.empty(int(L.pr_verifier_head_workspace_full(n)), dtype=torch.uint8, device=X.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     scores = torch.empty(n_req, dtype=torch.float32, device=X.device)
     st = L.pr_verifier_head(_ptr(X), n, _ptr(offsets), n_req, int(max_len if max_len is not None else max(n, 1)),

@@ -27,6 +27,7 @@ EXPORTED = (
     "pr_stream_finish", "pr_stream_reset_slots", "pr_stream_destroy", "pr_feature_sequence",
     "pr_verifier_head_workspace", "pr_verifier_head", "pr_calibrate_threshold",
     "pr_calibrate_workspace", "pr_sample_features", "pr_token_features_noalloc",
+    "pr_verifier_head_workspace_full",
 )
 
 PR_HEAD_WEIGHTS = 67329
@@ -81,6 +82,8 @@ def lib() -> C.CDLL:
     L.pr_feature_sequence.restype = C.c_int
     L.pr_verifier_head_workspace.argtypes = [i64]
     L.pr_verifier_head_workspace.restype = sz
+    L.pr_verifier_head_workspace_full.argtypes = [i64]
+    L.pr_verifier_head_workspace_full.restype = sz
     L.pr_verifier_head.argtypes = [vp, i64, vp, i32, i32, vp, vp, vp, sz, vp]
     L.pr_verifier_head.restype = C.c_int
     L.pr_request_aggregate.argtypes = [C.POINTER(TokenFeatures), vp, i32, C.POINTER(AggParams),

@@ -31,7 +31,7 @@ LIB = os.path.join(PKG, "libprouter.so")
 TOOLS_LIB = os.path.join(PKG, "libprtools.so")
 TOOLS_SOURCES = ["tools/prtools.hip"]
 
-SOURCES = ["row_features.hip", "topp.hip", "aggregate.hip", "head.hip", "calibrate.hip", "api.hip"]
+SOURCES = ["row_features.hip", "topp.hip", "aggregate.hip", "head.hip", "head_tiles.hip", "calibrate.hip", "api.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

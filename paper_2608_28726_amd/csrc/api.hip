@@ -244,7 +244,9 @@ pr_status pr_sample_features(const void* logits, pr_dtype dtype, int64_t n_rows,
   return hip_status(launch_sample(a, dtype, as_stream(stream)));
 }
 
-size_t pr_verifier_head_workspace(int64_t n_rows) { return n_rows > 0 ? head_workspace_bytes(n_rows) : 0; }
+size_t pr_verifier_head_workspace(int64_t n_rows) { return n_rows > 0 ? head_tiles_workspace_bytes(n_rows) : 0; }
+
+size_t pr_verifier_head_workspace_full(int64_t n_rows) { return n_rows > 0 ? head_workspace_bytes(n_rows) : 0; }
 
 pr_status pr_verifier_head(const float* X, int64_t n_rows, const int32_t* offsets, int32_t n_req, int32_t max_len,
                            const float* weights, float* scores, void* workspace, size_t workspace_bytes,
@@ -265,6 +267,7 @@ pr_status pr_verifier_head(const float* X, int64_t n_rows, const int32_t* offset
   a.weights = weights;
   a.scores = scores;
   a.ws = workspace;
+  if (workspace_bytes < pr_verifier_head_workspace_full(n_rows)) return hip_status(launch_head_tiles(a, as_stream(stream)));
   return hip_status(launch_head(a, as_stream(stream)));
 }
 

@@ -38,7 +38,12 @@ struct HeadArgs {
   int32_t* ctl;            // [0] number of blocks listed
 };
 
+// The head as one kernel per layer (head.hip) with head_workspace_bytes at
+// a.ws, or as separate tile kernels (head_tiles.hip) with the smaller
+// head_tiles_workspace_bytes.
 size_t head_workspace_bytes(int64_t n_rows);
 hipError_t launch_head(const HeadArgs& a, hipStream_t stream);
+size_t head_tiles_workspace_bytes(int64_t n_rows);
+hipError_t launch_head_tiles(const HeadArgs& a, hipStream_t stream);
 
 }  // namespace pr

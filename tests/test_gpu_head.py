@@ -142,14 +142,15 @@ def test_work_list_edges():
     assert np.array_equal(got.view(np.uint32), again.view(np.uint32))
 
 
+@pytest.mark.parametrize("full", [True, False])
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
 @pytest.mark.parametrize("first", [1, 2, 4, 13, 16, 33])
-def test_neighbours_share_row_groups(first, bad):
+def test_neighbours_share_row_groups(first, bad, full):
     """Requests that start and end inside the 16-row groups in which queries,
     keys and values are stored, and 1, 2 and more key tiles long, with an
     undefined request between them: its score alone is NaN, and the others
     are what the oracle gives for them. The workspace is exactly as long as
-    asked for, and nothing past it is written."""
+    asked for (either of the two sizes), and nothing past it is written."""
     lengths = [first, 3, 15, 17, 63, 1, 64, 66, 127, 130, 5]
     X, off = synthetic_sequence(lengths, 31)
     weights = wl.head_weights(seed=31)
@@ -158,7 +159,8 @@ def test_neighbours_share_row_groups(first, bad):
     for i in broken:
         Xb[off[i]:off[i + 1], 0] = bad
     Xd, offd = torch.tensor(Xb, device="cuda"), torch.tensor(off, device="cuda")
-    need = int(pr._abi.lib().pr_verifier_head_workspace(X.shape[0]))
+    L = pr._abi.lib()
+    need = int((L.pr_verifier_head_workspace_full if full else L.pr_verifier_head_workspace)(X.shape[0]))
     buf = torch.full((need + 4096,), 0x7F, dtype=torch.uint8, device="cuda")  # NaN patterns where nothing is written
     print(f"case head neighbours first={first} bad={bad} rows={X.shape[0]}", flush=True)
     got = pr.verifier_head(Xd, offd, torch.tensor(weights, device="cuda"), max_len=130, workspace=buf[:need])
