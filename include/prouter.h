@@ -212,6 +212,20 @@ pr_status pr_feature_sequence(const void* logits, pr_dtype dtype, int64_t n_rows
                               float* X, const pr_token_features_t* features, void* stream);
 
 /*
+ * pr_feature_sequence with a workspace, with which small batches spread each
+ * row over several workgroups; the results are the same. The first function
+ * gives the bytes it can use for a shape (0: none); with a smaller or NULL
+ * workspace the call is pr_feature_sequence.
+ *   workspace  device scratch, 16-byte aligned; no initialisation needed.
+ */
+size_t pr_feature_sequence_workspace(pr_dtype dtype, int64_t n_rows, int32_t vocab, int32_t top_p_on);
+pr_status pr_feature_sequence_ws(const void* logits, pr_dtype dtype, int64_t n_rows, int32_t vocab,
+                                 int64_t row_stride, const int32_t* sampled_ids, const float* temperature,
+                                 const float* top_p, const int32_t* offsets, int32_t n_req, int32_t top_k,
+                                 float* X, const pr_token_features_t* features, void* workspace,
+                                 size_t workspace_bytes, void* stream);
+
+/*
  * Fused sample-and-verify (the verifier reads the decoding distribution as a
  * side product of decoding, Sec. 3.1 and Sec. 4.1): one read of each row both
  * draws its token y_r from softmax(z_r / T_r) and computes the verifier's
@@ -248,6 +262,18 @@ pr_status pr_sample_features(const void* logits, pr_dtype dtype, int64_t n_rows,
                              const float* temperature, uint64_t seed, uint64_t offset, int32_t* sampled_ids,
                              const pr_token_features_t* features, const int32_t* offsets, int32_t n_req,
                              int32_t top_k, float* X, void* stream);
+
+/*
+ * pr_sample_features with a workspace, as pr_feature_sequence_ws is
+ * pr_feature_sequence with one: the same tokens and results. sequence_on: X
+ * is computed.
+ */
+size_t pr_sample_features_workspace(pr_dtype dtype, int64_t n_rows, int32_t vocab, int32_t sequence_on);
+pr_status pr_sample_features_ws(const void* logits, pr_dtype dtype, int64_t n_rows, int32_t vocab,
+                                int64_t row_stride, const float* temperature, uint64_t seed, uint64_t offset,
+                                int32_t* sampled_ids, const pr_token_features_t* features, const int32_t* offsets,
+                                int32_t n_req, int32_t top_k, float* X, void* workspace, size_t workspace_bytes,
+                                void* stream);
 
 /* The verifier head (Sec. 3.1, the paragraph after Eq. 3; Sec. 4.2): its
  * number of float32 parameters, the device workspace it needs, and the larger

@@ -185,9 +185,13 @@ def feature_sequence(logits: torch.Tensor, sampled_ids: torch.Tensor, temperatur
     X = torch.empty(n, 4, dtype=torch.float32, device=logits.device) if out is None else out
     feats = _alloc_features(n, logits.device) if features else None
     fs = C.byref(_features_struct(feats)) if feats is not None else None
-    st = _abi.lib().pr_feature_sequence(_ptr(logits), _dtype_code(logits), n, V, logits.stride(0),
-                                        _ptr(sampled_ids), _ptr(temperature), _ptr(top_p), _ptr(offsets),
-                                        offsets.shape[0] - 1, int(top_k), _ptr(X), fs, _stream_handle())
+    L = _abi.lib()
+    code = _dtype_code(logits)
+    need = int(L.pr_feature_sequence_workspace(code, n, V, int(top_p is not None)))
+    ws = torch.empty(need, dtype=torch.uint8, device=logits.device) if need else None
+    st = L.pr_feature_sequence_ws(_ptr(logits), code, n, V, logits.stride(0), _ptr(sampled_ids), _ptr(temperature),
+                                  _ptr(top_p), _ptr(offsets), offsets.shape[0] - 1, int(top_k), _ptr(X), fs, _ptr(ws),
+                                  need, _stream_handle())
     _abi.check("pr_feature_sequence", st)
     return (X, feats) if features else X
 
@@ -228,9 +232,13 @@ def sample_features(logits: torch.Tensor, temperature, seed: int, offset: int = 
             raise ValueError("offsets must be a contiguous 1-D int32 CUDA tensor")
         X = torch.empty(n, 4, dtype=torch.float32, device=logits.device)
         n_req = offsets.shape[0] - 1
-    st = _abi.lib().pr_sample_features(_ptr(logits), _dtype_code(logits), n, V, logits.stride(0), _ptr(temperature),
-                                       int(seed) & 0xFFFFFFFFFFFFFFFF, int(offset) & 0xFFFFFFFFFFFFFFFF, _ptr(ids),
-                                       fs, _ptr(offsets), n_req, int(top_k), _ptr(X), _stream_handle())
+    L = _abi.lib()
+    code = _dtype_code(logits)
+    need = int(L.pr_sample_features_workspace(code, n, V, int(X is not None)))
+    ws = torch.empty(need, dtype=torch.uint8, device=logits.device) if need else None
+    st = L.pr_sample_features_ws(_ptr(logits), code, n, V, logits.stride(0), _ptr(temperature),
+                                 int(seed) & 0xFFFFFFFFFFFFFFFF, int(offset) & 0xFFFFFFFFFFFFFFFF, _ptr(ids), fs,
+                                 _ptr(offsets), n_req, int(top_k), _ptr(X), _ptr(ws), need, _stream_handle())
     _abi.check("pr_sample_features", st)
     return ids, feats, X
 

@@ -27,7 +27,8 @@ EXPORTED = (
     "pr_stream_finish", "pr_stream_reset_slots", "pr_stream_destroy", "pr_feature_sequence",
     "pr_verifier_head_workspace", "pr_verifier_head", "pr_calibrate_threshold",
     "pr_calibrate_workspace", "pr_sample_features", "pr_token_features_noalloc",
-    "pr_verifier_head_workspace_full",
+    "pr_feature_sequence_workspace", "pr_feature_sequence_ws", "pr_sample_features_workspace",
+    "pr_sample_features_ws", "pr_verifier_head_workspace_full",
 )
 
 PR_HEAD_WEIGHTS = 67329
@@ -96,6 +97,16 @@ def lib() -> C.CDLL:
     L.pr_sample_features.argtypes = [vp, C.c_int, i64, i32, i64, vp, C.c_uint64, C.c_uint64, vp,
                                      C.POINTER(TokenFeatures), vp, i32, i32, vp, vp]
     L.pr_sample_features.restype = C.c_int
+    L.pr_feature_sequence_workspace.argtypes = [C.c_int, i64, i32, i32]
+    L.pr_feature_sequence_workspace.restype = sz
+    L.pr_feature_sequence_ws.argtypes = [vp, C.c_int, i64, i32, i64, vp, vp, vp, vp, i32, i32, vp,
+                                         C.POINTER(TokenFeatures), vp, sz, vp]
+    L.pr_feature_sequence_ws.restype = C.c_int
+    L.pr_sample_features_workspace.argtypes = [C.c_int, i64, i32, i32]
+    L.pr_sample_features_workspace.restype = sz
+    L.pr_sample_features_ws.argtypes = [vp, C.c_int, i64, i32, i64, vp, C.c_uint64, C.c_uint64, vp,
+                                        C.POINTER(TokenFeatures), vp, i32, i32, vp, vp, sz, vp]
+    L.pr_sample_features_ws.restype = C.c_int
     L.pr_calibrate_workspace.argtypes = [i32]
     L.pr_calibrate_workspace.restype = C.c_size_t
     L.pr_validate_offsets.argtypes = [vp, i32, i64, vp]

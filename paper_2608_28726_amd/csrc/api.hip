@@ -181,10 +181,23 @@ pr_status pr_token_features_noalloc(const void* logits, pr_dtype dtype, int64_t 
                            need, stream);
 }
 
+size_t pr_feature_sequence_workspace(pr_dtype dtype, int64_t n_rows, int32_t vocab, int32_t top_p_on) {
+  return top_p_on || vocab < 2 ? 0 : lane_workspace_bytes(n_rows, vocab, dtype, true, false);
+}
+
 pr_status pr_feature_sequence(const void* logits, pr_dtype dtype, int64_t n_rows, int32_t vocab,
                               int64_t row_stride, const int32_t* sampled_ids, const float* temperature,
                               const float* top_p, const int32_t* offsets, int32_t n_req, int32_t top_k,
                               float* X, const pr_token_features_t* features, void* stream) {
+  return pr_feature_sequence_ws(logits, dtype, n_rows, vocab, row_stride, sampled_ids, temperature, top_p, offsets,
+                                n_req, top_k, X, features, nullptr, 0, stream);
+}
+
+pr_status pr_feature_sequence_ws(const void* logits, pr_dtype dtype, int64_t n_rows, int32_t vocab,
+                                 int64_t row_stride, const int32_t* sampled_ids, const float* temperature,
+                                 const float* top_p, const int32_t* offsets, int32_t n_req, int32_t top_k,
+                                 float* X, const pr_token_features_t* features, void* workspace,
+                                 size_t workspace_bytes, void* stream) {
   pr_status st = check_rows(logits, dtype, n_rows, vocab, row_stride, sampled_ids, temperature);
   if (st != PR_OK) return st;
   if (top_k < 1 || top_k > PR_MAX_TOP_K || n_req < 0) return PR_ERR_INVALID_ARG;
@@ -206,14 +219,33 @@ pr_status pr_feature_sequence(const void* logits, pr_dtype dtype, int64_t n_rows
   a.n_req = n_req;
   a.top_k = top_k;
   if (top_p && vocab >= kTopPMaxVocab) return PR_ERR_UNSUPPORTED;
+  if (workspace && !aligned(workspace, 16)) return PR_ERR_INVALID_ARG;
   if (top_p) return hip_status(launch_topp(a, dtype, nullptr, as_stream(stream)));
+  const size_t need = lane_workspace_bytes(n_rows, vocab, dtype, true, false);
+  if (workspace && need > 0 && workspace_bytes >= need) {
+    a.G = lane_split(n_rows, vocab, dtype);
+    a.ws = static_cast<Partial*>(workspace);
+  }
   return hip_status(launch_feature_sequence(a, dtype, as_stream(stream)));
+}
+
+size_t pr_sample_features_workspace(pr_dtype dtype, int64_t n_rows, int32_t vocab, int32_t sequence_on) {
+  return vocab < 2 ? 0 : lane_workspace_bytes(n_rows, vocab, dtype, sequence_on != 0, true);
 }
 
 pr_status pr_sample_features(const void* logits, pr_dtype dtype, int64_t n_rows, int32_t vocab, int64_t row_stride,
                              const float* temperature, uint64_t seed, uint64_t offset, int32_t* sampled_ids,
                              const pr_token_features_t* features, const int32_t* offsets, int32_t n_req,
                              int32_t top_k, float* X, void* stream) {
+  return pr_sample_features_ws(logits, dtype, n_rows, vocab, row_stride, temperature, seed, offset, sampled_ids,
+                               features, offsets, n_req, top_k, X, nullptr, 0, stream);
+}
+
+pr_status pr_sample_features_ws(const void* logits, pr_dtype dtype, int64_t n_rows, int32_t vocab,
+                                int64_t row_stride, const float* temperature, uint64_t seed, uint64_t offset,
+                                int32_t* sampled_ids, const pr_token_features_t* features, const int32_t* offsets,
+                                int32_t n_req, int32_t top_k, float* X, void* workspace, size_t workspace_bytes,
+                                void* stream) {
   if (dtype != PR_F32 && dtype != PR_BF16) return PR_ERR_INVALID_ARG;
   if (n_rows < 0 || vocab < 2 || row_stride < vocab) return PR_ERR_INVALID_ARG;
   if (n_rows > (int64_t{1} << 26)) return PR_ERR_UNSUPPORTED;
@@ -241,6 +273,12 @@ pr_status pr_sample_features(const void* logits, pr_dtype dtype, int64_t n_rows,
   const uint64_t key = seed ^ (offset * 0x9E3779B97F4A7C15ull);
   a.key0 = static_cast<uint32_t>(key);
   a.key1 = static_cast<uint32_t>(key >> 32);
+  if (workspace && !aligned(workspace, 16)) return PR_ERR_INVALID_ARG;
+  const size_t need = lane_workspace_bytes(n_rows, vocab, dtype, X != nullptr, true);
+  if (workspace && need > 0 && workspace_bytes >= need) {
+    a.G = lane_split(n_rows, vocab, dtype);
+    a.ws = static_cast<Partial*>(workspace);
+  }
   return hip_status(launch_sample(a, dtype, as_stream(stream)));
 }
 

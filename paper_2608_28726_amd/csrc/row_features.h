@@ -67,17 +67,23 @@ __host__ __device__ inline RowMeta* split_meta(Partial* ws, int64_t n_rows, int 
   return reinterpret_cast<RowMeta*>(ws + n_rows * G);
 }
 
+// Workgroups per row of the sequence and sampling variants' lane-wise split
+// for a shape (1: none), and the workspace it takes.
+int lane_split(int64_t n_rows, int32_t V, pr_dtype dtype);
+size_t lane_workspace_bytes(int64_t n_rows, int32_t V, pr_dtype dtype, bool seq, bool sample);
+
 // One kernel when G == 1, partial-state and merge kernels otherwise; with
 // slot ids (streaming) each finalised row also updates its request slot.
 hipError_t launch_row_features(const RowArgs& a, pr_dtype dtype, hipStream_t stream);
 
 // The verifier input sequence X (with the features when a.out is set): one
-// workgroup per row, no split.
+// workgroup per row, or a.G with lane_workspace_bytes at a.ws.
 hipError_t launch_feature_sequence(const RowArgs& a, pr_dtype dtype, hipStream_t stream);
 
 // Fused sample-and-verify: each row's token is drawn in the same pass
 // (a.sampled_out), then its features (a.out, when set) and row of X (a.X,
-// when set) are written as for that token. One workgroup per row.
+// when set) are written as for that token. Workgroups per row as for the
+// sequence; the same tokens are drawn either way.
 hipError_t launch_sample(const RowArgs& a, pr_dtype dtype, hipStream_t stream);
 
 }  // namespace pr

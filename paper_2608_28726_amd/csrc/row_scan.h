@@ -216,18 +216,8 @@ __device__ __forceinline__ void consume_scalar(float z, int64_t idx, const RowCt
   }
 }
 
-// Block-wide merge of the lanes into one Partial (valid in thread 0). Each
-// wave reduces its lanes to a state relative to its own largest logit and
-// publishes it; after one barrier the first wave merges the NW wave states
-// with lane-parallel reductions.
-template <int BLOCK>
-__device__ __forceinline__ Partial block_merge(Lane& L, float c) {
-  constexpr int NW = BLOCK / kWave;
-  static_assert(NW >= 1 && NW <= kWave, "one wave merges the wave states");
-  __shared__ Partial sh[NW];
-  const int lane = threadIdx.x % kWave;
-  const int w = threadIdx.x / kWave;
-
+// State of the calling wave's lanes, relative to its own largest logit.
+__device__ __forceinline__ Partial wave_partial(Lane& L, float c) {
   Partial q;
   q.m = wave_max(L.t1);
   float S = L.S0 + L.S1, E = L.E0 + L.E1;
@@ -240,34 +230,51 @@ __device__ __forceinline__ Partial block_merge(Lane& L, float c) {
   wave_top2(q.t1, q.t1i, q.t2);
   q.cnt = wave_sum_u(L.cnt);
   q.pad = 0;
+  return q;
+}
+
+// Merge of the wave states held by the first `n` lanes of a wave, with
+// lane-parallel reductions; every lane gets the row's.
+__device__ __forceinline__ Partial merge_waves(Partial e, int n, float c) {
+  if (static_cast<int>(__lane_id()) >= n) {
+    e.m = -INFINITY;
+    e.S = 0.0f;
+    e.E = 0.0f;
+    e.t1 = -INFINITY;
+    e.t1i = kNoIndex;
+    e.t2 = -INFINITY;
+    e.cnt = 0;
+  }
+  Partial p;
+  p.m = wave_max(e.m);
+  rebase(e.m == -INFINITY, e.m * c, p.m * c, e.S, e.E);
+  p.S = wave_sum(e.S);
+  p.E = wave_sum(e.E);
+  wave_top2(e.t1, e.t1i, e.t2);
+  p.t1 = e.t1;
+  p.t1i = e.t1i;
+  p.t2 = e.t2;
+  p.cnt = wave_sum_u(e.cnt);
+  p.pad = 0;
+  return p;
+}
+
+// Block-wide merge of the lanes into one Partial (valid in thread 0). Each
+// wave reduces its lanes to a state relative to its own largest logit and
+// publishes it; after one barrier the first wave merges the NW wave states.
+template <int BLOCK>
+__device__ __forceinline__ Partial block_merge(Lane& L, float c) {
+  constexpr int NW = BLOCK / kWave;
+  static_assert(NW >= 1 && NW <= kWave, "one wave merges the wave states");
+  __shared__ Partial sh[NW];
+  const int lane = threadIdx.x % kWave;
+  const int w = threadIdx.x / kWave;
+  const Partial q = wave_partial(L, c);
   if (NW == 1) return q;
   if (lane == 0) sh[w] = q;
   __syncthreads();
   Partial p = q;
-  if (w == 0) {
-    Partial e;
-    if (lane < NW) {
-      e = sh[lane];
-    } else {
-      e.m = -INFINITY;
-      e.S = 0.0f;
-      e.E = 0.0f;
-      e.t1 = -INFINITY;
-      e.t1i = kNoIndex;
-      e.t2 = -INFINITY;
-      e.cnt = 0;
-      e.pad = 0;
-    }
-    p.m = wave_max(e.m);
-    rebase(e.m == -INFINITY, e.m * c, p.m * c, e.S, e.E);
-    p.S = wave_sum(e.S);
-    p.E = wave_sum(e.E);
-    wave_top2(e.t1, e.t1i, e.t2);
-    p.t1 = e.t1;
-    p.t1i = e.t1i;
-    p.t2 = e.t2;
-    p.cnt = wave_sum_u(e.cnt);
-  }
+  if (w == 0) p = merge_waves(lane < NW ? sh[lane] : q, NW, c);
   return p;
 }
 

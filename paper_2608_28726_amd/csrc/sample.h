@@ -71,6 +71,7 @@ __device__ __forceinline__ float unit(uint32_t w) { return static_cast<float>(w 
 struct Hook {
   uint32_t k0, k1;    // generator key (seed and offset)
   uint32_t row;       // counter word 0
+  uint32_t thread;    // the lane's place in the row's workgroup (counter word 1)
   int32_t s;          // vector steps taken (bucket s / kBucketSteps)
   float Wb;           // lane total before the current bucket
   float Wl;           // lane total after the last element taken in
@@ -79,7 +80,8 @@ struct Hook {
   uint32_t spare;     // second random word of the current pair of buckets
   int32_t win;        // chosen bucket: its first vector index (>= 0), -(element + 2) for a scalar, or kNone
 
-  __device__ __forceinline__ void init(uint32_t key0, uint32_t key1, int64_t r) {
+  __device__ __forceinline__ void init(uint32_t key0, uint32_t key1, int64_t r, uint32_t thr) {
+    thread = thr;
     k0 = key0;
     k1 = key1;
     row = static_cast<uint32_t>(r);
@@ -104,7 +106,7 @@ struct Hook {
     uint32_t w = spare;
     if ((b & 1) == 0) {
       uint32_t o1;
-      threefry2x32(row, (static_cast<uint32_t>(threadIdx.x) << 20) | static_cast<uint32_t>(b >> 1), k0, k1, w, o1);
+      threefry2x32(row, (thread << 20) | static_cast<uint32_t>(b >> 1), k0, k1, w, o1);
       spare = o1;
     }
     if (Wb < (1.0f - unit(w)) * Wl) win = bfirst;
@@ -154,7 +156,7 @@ struct Shared {
 // Every thread of the block calls this and gets the same (y, zy); y = -1
 // when the row's distribution is undefined.
 template <typename Tin, int BLOCK, int U>
-__device__ void pick(const void* row, int64_t nvec, const scan::RowCtx& cx, const scan::Lane& L, const Hook& hk,
+__device__ __forceinline__ void pick(const void* row, int64_t nvec, const scan::RowCtx& cx, const scan::Lane& L, const Hook& hk,
                      float A, bool defined, Shared& sh, int32_t& y, float& zy) {
   constexpr int VEC = Elem<Tin>::kVec;
   constexpr int NW = BLOCK / kWave;

@@ -120,7 +120,7 @@ struct Store {
 // keys; *gt receives the number of keys above the result (all of them when
 // fewer than j). Every thread calls it.
 template <int BLOCK, int PASSES, typename Keys>
-__device__ uint32_t select_desc(Keys&& keys, uint32_t j, const Lds& s, uint32_t* gt) {
+__device__ __forceinline__ uint32_t select_desc(Keys&& keys, uint32_t j, const Lds& s, uint32_t* gt) {
   static_assert(PASSES == 2 || PASSES == 4, "digits of 8 bits over 16 or 32 key bits");
   uint32_t prefix = 0, mask = 0, need = j;
   for (int b = threadIdx.x; b < 256; b += BLOCK) s.hist[b] = 0;
@@ -181,7 +181,7 @@ __device__ uint32_t select_desc(Keys&& keys, uint32_t j, const Lds& s, uint32_t*
 
 // Number of listed keys above kth (every thread gets it).
 template <int BLOCK>
-__device__ uint32_t count_above(const Lds& s, uint32_t n, uint32_t kth) {
+__device__ __forceinline__ uint32_t count_above(const Lds& s, uint32_t n, uint32_t kth) {
   uint32_t c = 0;
   for (uint32_t e = threadIdx.x; e < n; e += BLOCK) c += s.key[e] > kth ? 1u : 0u;
   c = wave_sum_u(c);
@@ -197,7 +197,7 @@ __device__ uint32_t count_above(const Lds& s, uint32_t n, uint32_t kth) {
 // Keeps the listed keys above kth (fewer than kMaxK of them) and drops the
 // rest. Returns the new list length.
 template <int BLOCK>
-__device__ uint32_t compact(const Lds& s, uint32_t n, uint32_t kth) {
+__device__ __forceinline__ uint32_t compact(const Lds& s, uint32_t n, uint32_t kth) {
   if (threadIdx.x == 0) s.misc[kNSmall] = 0;
   __syncthreads();
   for (uint32_t e = threadIdx.x; e < n; e += BLOCK) {

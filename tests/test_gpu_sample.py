@@ -241,3 +241,50 @@ def test_full_size_draws_are_consistent():
     assert (g["rank"] == -1).all()
     g["rank"] = o["rank"].copy()
     compare_features(g, o, what="full-size drawn ")
+
+
+def _calls_without_workspace(monkeypatch):
+    """The binding's calls as they are with no workspace: one workgroup per row."""
+    L = pr._abi.lib()
+    monkeypatch.setattr(L, "pr_sample_features_workspace", lambda *a: 0)
+    monkeypatch.setattr(L, "pr_feature_sequence_workspace", lambda *a: 0)
+
+
+@pytest.mark.parametrize("dtype,V", [("bf16", 50003), ("bf16", 65536), ("f32", 25000), ("f32", 32771)])
+@pytest.mark.parametrize("n", [1, 7, 64])
+def test_split_rows_are_bit_identical(monkeypatch, n, dtype, V):
+    """Rows scanned by sixteen workgroups (batches of up to 64 rows of 100,000
+    bytes or more) give the tokens, features and sequence rows of the one
+    workgroup bit for bit: aligned and unaligned rows, masked logits, ties
+    across the split, rows without a distribution."""
+    g = torch.Generator().manual_seed(V + n)
+    z = torch.randn((n, V + 1), generator=g) * torch.linspace(0.5, 4.0, n).unsqueeze(1)
+    z[:, ::97] = -math.inf
+    z[0, 5::1000] = 20.0
+    if n >= 7:
+        z[3, 1:] = -math.inf      # no distribution
+        z[4, 77] = math.nan
+        z[5, 1:] = 1.25           # every logit tied
+    z = z.to(torch.float32 if dtype == "f32" else torch.bfloat16).cuda()
+    T = torch.full((n,), 0.8, device="cuda")
+    T[n // 2] = -1.0 if n >= 7 else 0.8
+    off = torch.tensor([0, (n + 1) // 2, n], dtype=torch.int32, device="cuda")
+    ids = torch.randint(0, V, (n,), generator=g, dtype=torch.int32).cuda()
+    for start in (0, 1):  # aligned rows, when the row stride is, and rows off by one element
+        rows = z[:, start:start + V]
+        assert (pr._abi.lib().pr_sample_features_workspace(pr._dtype_code(rows), n, V, 0) > 0)
+        got = pr.sample_features(rows, T, seed=5, offset=2, offsets=off), pr.sample_features(rows, T, seed=5, offset=3)
+        seq = pr.feature_sequence(rows, ids, T, off, features=True)
+        with monkeypatch.context() as m:
+            _calls_without_workspace(m)
+            ref = pr.sample_features(rows, T, seed=5, offset=2, offsets=off), pr.sample_features(rows, T, seed=5, offset=3)
+            sref = pr.feature_sequence(rows, ids, T, off, features=True)
+        torch.cuda.synchronize()
+        for (i1, f1, x1), (i0, f0, x0) in zip(got, ref):
+            assert torch.equal(i1, i0)
+            for k in f0:
+                assert torch.equal(f1[k].view(torch.int32), f0[k].view(torch.int32)), k
+            assert x0 is None or torch.equal(x1.view(torch.int32), x0.view(torch.int32))
+        assert torch.equal(seq[0].view(torch.int32), sref[0].view(torch.int32))
+        for k in sref[1]:
+            assert torch.equal(seq[1][k].view(torch.int32), sref[1][k].view(torch.int32)), k
