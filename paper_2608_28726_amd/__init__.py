@@ -36,12 +36,20 @@ FEATURE_INTS = ("rank", "argmax", "cutoff")
 _LINKS = {"identity": 0, "sigmoid": 1}
 
 
-def _stream_handle() -> C.c_void_p:
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+# What a call costs on the host is most of a small batch's time: pointers go to
+# ctypes as plain ints, and the current stream's handle is read without making
+# a Stream object (1.5 us a call).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
-def _ptr(t) -> C.c_void_p | None:
-    return None if t is None else C.c_void_p(t.data_ptr())
+def _stream_handle() -> int:
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
+
+
+def _ptr(t) -> int | None:
+    return None if t is None else t.data_ptr()
 
 
 def _dtype_code(logits: torch.Tensor) -> int:
@@ -55,13 +63,11 @@ def _dtype_code(logits: torch.Tensor) -> int:
 def _check_rows(logits, sampled_ids, temperature, top_p):
     if not logits.is_cuda or logits.dim() != 2 or logits.stride(1) != 1:
         raise ValueError("logits must be a 2-D CUDA tensor with unit stride along the vocabulary")
-    n = logits.shape[0]
+    shape = (logits.shape[0],)
     for name, t, dt in (("sampled_ids", sampled_ids, torch.int32), ("temperature", temperature, torch.float32),
                         ("top_p", top_p, torch.float32)):
-        if t is None:
-            continue
-        if t.dtype != dt or not t.is_cuda or t.dim() != 1 or t.shape[0] != n or not t.is_contiguous():
-            raise ValueError(f"{name} must be a contiguous 1-D {dt} CUDA tensor of length {n}")
+        if t is not None and (t.dtype != dt or not t.is_cuda or t.shape != shape or not t.is_contiguous()):
+            raise ValueError(f"{name} must be a contiguous 1-D {dt} CUDA tensor of length {shape[0]}")
 
 
 def _check_features(f: dict, device, n: int | None, what: str, fields=_abi.FEATURE_FIELDS):
@@ -71,7 +77,7 @@ def _check_features(f: dict, device, n: int | None, what: str, fields=_abi.FEATU
     for k in fields:
         t = f.get(k)
         dt = torch.float32 if k in FEATURE_FLOATS else torch.int32
-        if (t is None or t.dtype != dt or t.device != device or t.dim() != 1 or not t.is_contiguous()
+        if (t is None or t.dtype != dt or t.dim() != 1 or t.device != device or not t.is_contiguous()
                 or (n is not None and t.shape[0] != n)):
             size = "" if n is None else f" of length {n}"
             raise ValueError(f"{what}['{k}'] must be a contiguous 1-D {dt} tensor{size} on {device}")
@@ -95,15 +101,20 @@ def _as_row_tensor(x, n, device):
     return x
 
 
+_INT_FIELDS = FEATURE_INTS + ("flags",)  # flags: uint32 bits
+assert FEATURE_FLOATS + _INT_FIELDS == _abi.FEATURE_FIELDS
+
+
 def _alloc_features(n: int, device) -> dict:
-    out = {k: torch.empty(n, dtype=torch.float32, device=device) for k in FEATURE_FLOATS}
-    out.update({k: torch.empty(n, dtype=torch.int32, device=device) for k in FEATURE_INTS})
-    out["flags"] = torch.empty(n, dtype=torch.int32, device=device)  # uint32 bits
+    """The ten per-token outputs: rows of one float32 and one int32 allocation
+    (an allocation a field took twice as long as the kernel launch)."""
+    out = dict(zip(FEATURE_FLOATS, torch.empty((len(FEATURE_FLOATS), n), dtype=torch.float32, device=device).unbind(0)))
+    out.update(zip(_INT_FIELDS, torch.empty((len(_INT_FIELDS), n), dtype=torch.int32, device=device).unbind(0)))
     return out
 
 
 def _features_struct(f: dict) -> _abi.TokenFeatures:
-    return _abi.TokenFeatures(*[f[k].data_ptr() if f.get(k) is not None else None for k in _abi.FEATURE_FIELDS])
+    return _abi.TokenFeatures(*[t.data_ptr() if t is not None else None for t in map(f.get, _abi.FEATURE_FIELDS)])
 
 
 def token_features_workspace(logits: torch.Tensor, top_p_on: bool = False) -> int:
@@ -130,7 +141,7 @@ def token_features(logits: torch.Tensor, sampled_ids: torch.Tensor, temperature,
     else:
         _check_features(out, logits.device, n, "out")
     _check_workspace(workspace, logits.device)
-    need = int(L.pr_token_features_workspace(code, n, V, int(top_p is not None)))
+    need = L.pr_token_features_workspace(code, n, V, int(top_p is not None))
     if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
         workspace = torch.empty(need, dtype=torch.uint8, device=logits.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
@@ -273,9 +284,16 @@ def verifier_head(X: torch.Tensor, offsets: torch.Tensor, weights: torch.Tensor,
     return scores
 
 
+_default_params = None
+
+
 def _params(q=0.1, weights=None, bias=0.0, link="identity") -> _abi.AggParams:
-    p = _abi.AggParams()
-    _abi.lib().pr_agg_params_default(C.byref(p))
+    global _default_params
+    if _default_params is None:  # the library's defaults, which never change
+        p = _abi.AggParams()
+        _abi.lib().pr_agg_params_default(C.byref(p))
+        _default_params = bytes(p)
+    p = _abi.AggParams.from_buffer_copy(_default_params)
     p.q = float(q)
     if weights is not None:
         w = [float(v) for v in torch.as_tensor(weights, dtype=torch.float64).reshape(-1).tolist()]
@@ -289,15 +307,13 @@ def _params(q=0.1, weights=None, bias=0.0, link="identity") -> _abi.AggParams:
 
 
 def _alloc_agg(n: int, device) -> dict:
-    return {"count": torch.empty(n, dtype=torch.int32, device=device),
-            "mean": torch.empty(n, 4, dtype=torch.float32, device=device),
-            "min": torch.empty(n, 4, dtype=torch.float32, device=device),
-            "quant": torch.empty(n, 4, dtype=torch.float32, device=device),
+    mean, mn, quant = torch.empty((3, n, 4), dtype=torch.float32, device=device).unbind(0)
+    return {"count": torch.empty(n, dtype=torch.int32, device=device), "mean": mean, "min": mn, "quant": quant,
             "score": torch.empty(n, dtype=torch.float32, device=device)}
 
 
 def _agg_struct(a: dict) -> _abi.RequestAgg:
-    return _abi.RequestAgg(*[a[k].data_ptr() if a.get(k) is not None else None for k in _abi.AGG_FIELDS])
+    return _abi.RequestAgg(*[t.data_ptr() if t is not None else None for t in map(a.get, _abi.AGG_FIELDS)])
 
 
 def request_aggregate(feats: dict, offsets: torch.Tensor, q: float = 0.1, weights=None, bias: float = 0.0,
