@@ -131,6 +131,9 @@ void pr_agg_params_default(pr_agg_params* params);
  * none). top_p_on: 1 if a top-p array will be passed.
  */
 size_t pr_token_features_workspace(pr_dtype dtype, int64_t n_rows, int32_t vocab, int32_t top_p_on);
+/* The bytes with which small batches run fastest (top-p rows are then spread
+ * over several workgroups each); at least pr_token_features_workspace. */
+size_t pr_token_features_workspace_full(pr_dtype dtype, int64_t n_rows, int32_t vocab, int32_t top_p_on);
 
 /*
  * Per-token features of n_rows logit rows (Sec. 3.1, Eq. 3, extended to the

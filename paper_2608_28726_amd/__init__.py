@@ -141,9 +141,11 @@ def token_features(logits: torch.Tensor, sampled_ids: torch.Tensor, temperature,
     else:
         _check_features(out, logits.device, n, "out")
     _check_workspace(workspace, logits.device)
-    need = L.pr_token_features_workspace(code, n, V, int(top_p is not None))
-    if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = torch.empty(need, dtype=torch.uint8, device=logits.device)
+    top_p_on = int(top_p is not None)
+    if workspace is None or (workspace.numel() * workspace.element_size()
+                             < L.pr_token_features_workspace(code, n, V, top_p_on)):
+        full = L.pr_token_features_workspace_full(code, n, V, top_p_on)
+        workspace = torch.empty(full, dtype=torch.uint8, device=logits.device) if full else None
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     st = L.pr_token_features(_ptr(logits), code, n, V, logits.stride(0), _ptr(sampled_ids), _ptr(temperature),
                              _ptr(top_p), C.byref(_features_struct(out)), _ptr(workspace), ws_bytes,

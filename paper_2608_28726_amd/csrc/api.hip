@@ -23,6 +23,8 @@ struct pr_stream {
   StreamDev dev;
   pr_agg_params params;
   Partial* ws;  // split-row workspace for up to max_slots rows of kStreamMaxSplit workgroups
+  void* tws;    // the same for top-p steps of few rows
+  size_t tws_bytes;
   void* block;  // single allocation backing everything above
 };
 
@@ -137,6 +139,11 @@ size_t pr_token_features_workspace(pr_dtype dtype, int64_t n_rows, int32_t vocab
   return split_workspace_bytes(n_rows, row_split(n_rows, vocab, dtype));
 }
 
+size_t pr_token_features_workspace_full(pr_dtype dtype, int64_t n_rows, int32_t vocab, int32_t top_p_on) {
+  if (n_rows <= 0 || vocab < 2) return 0;
+  return top_p_on ? topp_split_workspace(n_rows, vocab) : pr_token_features_workspace(dtype, n_rows, vocab, 0);
+}
+
 pr_status pr_token_features(const void* logits, pr_dtype dtype, int64_t n_rows, int32_t vocab,
                             int64_t row_stride, const int32_t* sampled_ids, const float* temperature,
                             const float* top_p, const pr_token_features_t* out, void* workspace,
@@ -157,7 +164,10 @@ pr_status pr_token_features(const void* logits, pr_dtype dtype, int64_t n_rows, 
   a.top_p = top_p;
   a.out = *out;
   if (top_p && vocab >= kTopPMaxVocab) return PR_ERR_UNSUPPORTED;
-  if (top_p) return hip_status(launch_topp(a, dtype, workspace, as_stream(stream)));
+  if (top_p) {
+    if (!aligned(workspace, 16)) workspace = nullptr;
+    return hip_status(launch_topp(a, dtype, workspace, workspace_bytes, as_stream(stream)));
+  }
   a.G = row_split(n_rows, vocab, dtype);
   a.ws = static_cast<Partial*>(workspace);
   return hip_status(launch_row_features(a, dtype, as_stream(stream)));
@@ -220,7 +230,7 @@ pr_status pr_feature_sequence_ws(const void* logits, pr_dtype dtype, int64_t n_r
   a.top_k = top_k;
   if (top_p && vocab >= kTopPMaxVocab) return PR_ERR_UNSUPPORTED;
   if (workspace && !aligned(workspace, 16)) return PR_ERR_INVALID_ARG;
-  if (top_p) return hip_status(launch_topp(a, dtype, nullptr, as_stream(stream)));
+  if (top_p) return hip_status(launch_topp(a, dtype, nullptr, 0, as_stream(stream)));
   const size_t need = lane_workspace_bytes(n_rows, vocab, dtype, true, false);
   if (workspace && need > 0 && workspace_bytes >= need) {
     a.G = lane_split(n_rows, vocab, dtype);
@@ -374,7 +384,8 @@ pr_status pr_stream_create(int32_t max_slots, int32_t max_len, const pr_agg_para
   const bool bounded = max_len == 0;  // P-square markers instead of the history
   const size_t b_p2q = bounded ? up(S * 20 * sizeof(double)) : 0;
   const size_t b_p2n = bounded ? up(S * 16 * sizeof(int32_t)) : 0;
-  const size_t total = b_ws + b_sum + b_hist + b_min + b_cnt + b_nan + b_p2q + b_p2n;
+  const size_t b_tws = up(topp_split_workspace_most(static_cast<int64_t>(S)));
+  const size_t total = b_ws + b_sum + b_hist + b_min + b_cnt + b_nan + b_p2q + b_p2n + b_tws;
   pr_stream* s = new (std::nothrow) pr_stream();
   if (!s) return PR_ERR_NO_MEMORY;
   hipError_t e = hipGetDevice(&s->device);
@@ -399,6 +410,9 @@ pr_status pr_stream_create(int32_t max_slots, int32_t max_len, const pr_agg_para
   s->dev.p2q = bounded ? reinterpret_cast<double*>(b) : nullptr;
   b += b_p2q;
   s->dev.p2n = bounded ? reinterpret_cast<int32_t*>(b) : nullptr;
+  b += b_p2n;
+  s->tws = b;
+  s->tws_bytes = b_tws;
   s->dev.p2p = p.q;
   if (bounded) s->dev.hist = nullptr;
   s->dev.max_slots = max_slots;
@@ -442,7 +456,7 @@ pr_status pr_stream_step(pr_stream* state, const void* logits, pr_dtype dtype, i
   a.ws = state->ws;
   a.slot_ids = slot_ids;
   a.st = state->dev;
-  if (top_p) return hip_status(launch_topp(a, dtype, nullptr, as_stream(stream)));
+  if (top_p) return hip_status(launch_topp(a, dtype, state->tws, state->tws_bytes, as_stream(stream)));
   return hip_status(launch_row_features(a, dtype, as_stream(stream)));
 }
 

@@ -36,6 +36,10 @@
 // method (Tang, ACM TOMS 15(2), 1989): exp(d) = 2^(n/64) * exp(r) with
 // |r| <= ln2/128 and a degree-5 polynomial.
 //
+// Small batches of long rows spread each row over eight workgroups, in four
+// kernels (see topp_scan_kernel); the rest of this text is the form with one
+// workgroup per row.
+//
 // When the histogram cannot be used (no finite anchor, an overfull list or
 // window, or a crossing outside the window) the row falls back to the
 // three-pass method: a 4096-bin float64 histogram relative to M, exact sums
@@ -45,6 +49,7 @@
 // boundary value) that resolves ties by counting.
 #include "topp.h"
 
+#include <limits>
 #include <type_traits>
 
 #include "p2.h"
@@ -325,6 +330,19 @@ struct HistHook {
     }
   }
 };
+
+// The hook's map for a row of temperature T anchored at A0 (not anchored:
+// nothing is binned).
+__device__ __forceinline__ void set_hook(HistHook& hk, TpShared& sh, float T, float A0, bool anchored) {
+  const float invT = 1.0f / T;
+  hk.bins = sh.u.hs.bins;
+  hk.above = sh.above;
+  hk.n_above = &sh.n_above;
+  hk.kz = anchored ? -invT * kHK : 0.0f;
+  hk.k0 = anchored ? fmaf(A0, invT * kHK, kHAbove * kHK) : INFINITY;
+  hk.kz4 = hk.kz * kOffQ;
+  hk.k04 = hk.k0 * kOffQ;
+}
 
 // Bitonic sort of sh.win[0..n2) into descending order (n2 a power of two).
 __device__ __forceinline__ void bitonic_desc(float* a, int n2) {
@@ -1196,13 +1214,12 @@ __device__ __forceinline__ bool approx_cut(const void* row, int32_t V, int64_t h
   return true;
 }
 
-// The nucleus from the stats-pass histogram and one exact pass (sparse when
-// few buckets can reach the window, else dense). Returns false (and leaves
-// nuc unset) when the row must take the three-pass method. tk holds each
-// lane's three largest bucket maxima and the steps of the first two.
-template <typename Tin>
-__device__ __forceinline__ bool hist_nucleus(const void* row, int32_t V, int64_t h, int64_t nvec, const Dist& D, float P,
-                             float A0, const HistHook& hk, const topk::Hook& tk, TpShared& sh, Nucleus& nuc) {
+// Step 1 of the histogram method: the window of bins around P of the total.
+// n_full: threads for which full(W) holds. Returns false when the row must
+// take the three-pass method.
+template <typename Full>
+__device__ __forceinline__ bool locate_window(const Dist& D, float P, const HistHook& hk, TpShared& sh, Window& W,
+                                              uint32_t& n_full, Full full) {
   const double* tab = sh.exptab;
   const uint32_t n_above = sh.n_above;
   if (n_above > static_cast<uint32_t>(kAboveCap)) return false;
@@ -1223,7 +1240,6 @@ __device__ __forceinline__ bool hist_nucleus(const void* row, int32_t V, int64_t
   // the centre (relative error below kBinMassRelErr per logit).
   const double hb = -D.invT64 / static_cast<double>(hk.kz);
   const double lead = -(static_cast<double>(D.M) + static_cast<double>(hk.k0) / static_cast<double>(hk.kz)) * D.invT64;
-  const double invK = 1.0 / static_cast<double>(kHK);
   // Kept compact (it runs once per row): the loops over a thread's kPer bins
   // are not unrolled (one copy of the float64 exp each; the second loop
   // recomputes the masses of the first), and the crossing bins are found
@@ -1307,7 +1323,6 @@ __device__ __forceinline__ bool hist_nucleus(const void* row, int32_t V, int64_t
     }
   }
   __syncthreads();
-  Window W;
   W.b_lo = sa >= t_lo ? -1 : sh.hb_lo;  // -1: the list above the bins
   W.b_hi = sa >= t_hi ? -1 : sh.hb_hi;
   uint32_t inwin = 0, above = 0;
@@ -1328,14 +1343,8 @@ __device__ __forceinline__ bool hist_nucleus(const void* row, int32_t V, int64_t
       }
     }
   }
-  // Sparse pass when few lanes have three buckets reaching the window: a
-  // bucket can reach it only if its maximum does (bf falls with z).
-  auto reaches = [&](float x) { return fmaf(x, hk.kz4, hk.k04) < static_cast<float>(W.b_hi + 1) * kOffQ; };
-  const bool full = reaches(tk.b3);
-  const int64_t s1 = (tk.b1v >= 0 && reaches(tk.b1)) ? tk.b1v : -1;
-  const int64_t s2 = (tk.b2v >= 0 && reaches(tk.b2)) ? tk.b2v : -1;
-  {  // one exchange for the counts, the lanes with a third bucket reaching the window and the sums below it
-    const uint32_t inwin_w = wave_sum_u(inwin), above_w = wave_sum_u(above), full_w = wave_sum_u(full ? 1u : 0u);
+  {  // one exchange for the counts, the threads for which full(W) holds and the sums below the window
+    const uint32_t inwin_w = wave_sum_u(inwin), above_w = wave_sum_u(above), full_w = wave_sum_u(full(W) ? 1u : 0u);
     const double sb_w = wave_sum_d(sb), sbm_w = wave_sum_d(sb_max);
     if (lane == 0) {
       sh.loc.u[0][wv] = inwin_w;
@@ -1347,7 +1356,7 @@ __device__ __forceinline__ bool hist_nucleus(const void* row, int32_t V, int64_t
   }
   __syncthreads();  // also: every bin is read before the table below overwrites them
   inwin = above = 0u;
-  uint32_t n_full = 0u;
+  n_full = 0u;
   sb = sb_max = 0.0;
   for (int k = 0; k < kNW; ++k) {
     inwin += sh.loc.u[0][k];
@@ -1360,7 +1369,28 @@ __device__ __forceinline__ bool hist_nucleus(const void* row, int32_t V, int64_t
   W.above = above + (W.b_lo >= 0 ? n_above : 0u);  // counts are exact
   W.s_below = sb;
   W.s_below_err = kBinMassRelErr * 1.01 * sb_max;  // 1.01: a logit's mass is below 1.0093 w_b
-  if (W.inwin > static_cast<uint32_t>(kCap)) return false;
+  return W.inwin <= static_cast<uint32_t>(kCap);
+}
+
+// The nucleus from the stats-pass histogram and one exact pass (sparse when
+// few buckets can reach the window, else dense). Returns false (and leaves
+// nuc unset) when the row must take the three-pass method. tk holds each
+// lane's three largest bucket maxima and the steps of the first two.
+template <typename Tin>
+__device__ __forceinline__ bool hist_nucleus(const void* row, int32_t V, int64_t h, int64_t nvec, const Dist& D, float P,
+                             float A0, const HistHook& hk, const topk::Hook& tk, TpShared& sh, Nucleus& nuc) {
+  Window W;
+  uint32_t n_full;
+  // Sparse pass when few lanes have three buckets reaching the window: a
+  // bucket can reach it only if its maximum does (bf falls with z).
+  auto reaches = [&](float x) { return fmaf(x, hk.kz4, hk.k04) < static_cast<float>(W.b_hi + 1) * kOffQ; };
+  if (!locate_window(D, P, hk, sh, W, n_full, [&](const Window&) { return reaches(tk.b3); })) return false;
+  const bool full = reaches(tk.b3);
+  const int64_t s1 = (tk.b1v >= 0 && reaches(tk.b1)) ? tk.b1v : -1;
+  const int64_t s2 = (tk.b2v >= 0 && reaches(tk.b2)) ? tk.b2v : -1;
+  const double invK = 1.0 / static_cast<double>(kHK);
+  constexpr int kPer = kHB / kTpBlock;
+  const int b0 = threadIdx.x * kPer;
   // The counts are consumed: the same LDS now holds exp(centre of bin b - M).
   // A logit of bin b is exp(dd) = wtab[b] * exp(r), r = dd - centre, |r| at
   // most half a bin (0.0092 nats) plus the float32 rounding of bf (see
@@ -1486,20 +1516,13 @@ __global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) v
   const float Prow = a.top_p[r];
   const bool nucleus_row = Prow > 0.0f && Prow < 1.0f && temperature_ok(cx.T);
   const bool anchored = nucleus_row && A0 > -INFINITY && A0 < INFINITY;
-  const float invT = 1.0f / cx.T;
   // The top-K hook keeps each lane's three largest bucket maxima and the
   // steps of the first two: the sparse exact pass reads those buckets back
   // (and the sequence variant selects the K largest logits from them).
   HookPair<HistHook, topk::Hook> hp;
   HistHook& hk = hp.a;
   hp.b.init();
-  hk.bins = sh.u.hs.bins;
-  hk.above = sh.above;
-  hk.n_above = &sh.n_above;
-  hk.kz = anchored ? -invT * kHK : 0.0f;
-  hk.k0 = anchored ? fmaf(A0, invT * kHK, kHAbove * kHK) : INFINITY;  // unanchored: nothing binned
-  hk.kz4 = hk.kz * kOffQ;
-  hk.k04 = hk.k0 * kOffQ;
+  set_hook(hk, sh, cx.T, A0, anchored);
 
   // 1. stats pass, building the histogram (S and E of the merged state are
   // only formed for a row without a nucleus)
@@ -1572,12 +1595,347 @@ __global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) v
   finish_row(a, r, p, cx, fix, &nuc);
 }
 
+// ---- small batches: a row over kParts workgroups ----
+//
+// One workgroup per row leaves most of the chip idle on a decode step's rows,
+// and a row's passes are bound by one CU's LDS atomics and arithmetic. Here
+// the two passes over the logits are spread over kParts workgroups per row,
+// with the steps between them in one workgroup per row, as four kernels:
+// scan (the stats pass and a histogram of each part), locate (the sums of the
+// histograms, the window), sum (float64 masses above the window and in total,
+// the window's logits gathered) and cut. The sums are those of the float64
+// pass, taken per part and added in part order; a row that the histogram
+// method cannot decide takes the three-pass method in the cut kernel.
+constexpr int kParts = 8;
+
+enum : int32_t { kRowPlain = 0, kRowSplit = 1, kRowThreePass = 2 };
+
+struct TpRowState {  // a row between the kernels
+  Partial p;
+  Window W;
+  float A0;
+  int32_t state;
+  uint32_t wcount;  // logits gathered
+  uint32_t fix;
+};
+struct TpPart {  // one part of a row
+  uint64_t bins[kHB];
+  float above[kAboveCap];
+  Partial p;
+  double sT, mA, eA;
+  uint32_t n_above, fix;
+};
+struct TpRowWs {
+  TpPart part[kParts];
+  float win[kCap];
+  TpRowState row;
+};
+static_assert(sizeof(TpRowWs) % 16 == 0 && sizeof(TpPart) % 16 == 0, "16-byte aligned arrays");
+
+__device__ __forceinline__ TpRowWs& row_ws(const RowArgs& a, int64_t r) {
+  return reinterpret_cast<TpRowWs*>(a.ws)[r];
+}
+
+// Largest of the row's first kTpBlock vectors, the anchor of every part's
+// histogram; every thread gets it.
+template <typename Tin>
+__device__ __forceinline__ float row_anchor(const void* row, int64_t h, int64_t nvec, TpShared& sh) {
+  constexpr int VEC = Elem<Tin>::kVec;
+  const vec4u* vp = reinterpret_cast<const vec4u*>(static_cast<const Tin*>(row) + h);
+  float z[VEC];
+  Elem<Tin>::unpack(static_cast<int64_t>(threadIdx.x) < nvec ? vp[threadIdx.x] : neg_inf_vec<Tin>(), z);
+  float m = z[0];
+#pragma unroll
+  for (int k = 1; k < VEC; ++k) m = fmaxf(m, z[k]);
+  m = wave_max(m);
+  if (threadIdx.x % kWave == 0) sh.red_f[threadIdx.x / kWave] = m;
+  __syncthreads();
+  m = sh.red_f[0];
+  for (int k = 1; k < kNW; ++k) m = fmaxf(m, sh.red_f[k]);
+  return m;
+}
+
+template <typename Tin>
+__global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) void topp_scan_kernel(RowArgs a) {
+  __shared__ TpShared sh;
+  const int64_t r = blockIdx.x / kParts;
+  const int g = blockIdx.x % kParts;
+  if (r >= a.n_rows) return;
+  constexpr int VEC = Elem<Tin>::kVec;
+  const void* row = static_cast<const Tin*>(a.logits) + r * a.row_stride;
+  const int64_t h = head_elems<Tin>(row, a.V);
+  const int64_t nvec = (a.V - h) / VEC;
+  const int64_t vb = nvec * g / kParts, ve = nvec * (g + 1) / kParts;
+  constexpr int kLD = first_pass_depth<Tin>();
+  vec4u v[kLD];
+  stretch_prefetch<Tin, kTpBlock, kLD>(row, h, vb, ve, v);
+  const RowCtx cx = row_ctx<Tin>(a, r, row);
+  for (int b = threadIdx.x; b < kHB; b += kTpBlock) sh.u.hs.bins[b] = 0;
+  if (threadIdx.x == 0) sh.n_above = 0;
+  const float A0 = row_anchor<Tin>(row, h, nvec, sh);  // its barrier also ends the clearing
+  const float P = a.top_p[r];
+  const bool nucleus_row = P > 0.0f && P < 1.0f && temperature_ok(cx.T);
+  const bool anchored = nucleus_row && A0 > -INFINITY && A0 < INFINITY;
+  HistHook hk;
+  set_hook(hk, sh, cx.T, A0, anchored);
+  Lane L;
+  lane_init(L);
+  if (nucleus_row) {
+    [[clang::always_inline]] scan_stretch<Tin, kTpBlock, 2, kLD, false, false>(row, a.V, vb, ve, g == 0,
+                                                                               g == kParts - 1, nvec, cx, L, v, hk);
+  } else {
+    [[clang::always_inline]] scan_stretch<Tin, kTpBlock, 2, kLD, false, true>(row, a.V, vb, ve, g == 0,
+                                                                              g == kParts - 1, nvec, cx, L, v,
+                                                                              NoHook());
+  }
+  const Partial p = block_merge<kTpBlock>(L, cx.c);  // its barrier also ends the counting
+  TpRowWs& w = row_ws(a, r);
+  TpPart& o = w.part[g];
+  if (g == 0) {  // the row's rank corrections
+    const uint32_t fix = rank_fixup<Tin, kTpBlock>(row, a.V, nvec, cx);
+    if (threadIdx.x == 0) {
+      w.row.fix = fix;
+      w.row.A0 = A0;
+    }
+  }
+  if (threadIdx.x == 0) {
+    o.p = p;
+    o.n_above = sh.n_above;
+  }
+  if (!anchored) return;
+  typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+  for (int b = threadIdx.x; b < kHB / 2; b += kTpBlock)
+    reinterpret_cast<u64x2*>(o.bins)[b] = reinterpret_cast<const u64x2*>(sh.u.hs.bins)[b];
+  const uint32_t n = min(sh.n_above, static_cast<uint32_t>(kAboveCap));
+  if (threadIdx.x < n) o.above[threadIdx.x] = sh.above[threadIdx.x];
+}
+
+// The row's distance map from its merged state.
+__device__ __forceinline__ Dist row_dist(const Partial& p, float T) {
+  Dist D;
+  D.M = p.m;
+  D.invT = 1.0f / T;
+  D.invT64 = 1.0 / static_cast<double>(T);
+  return D;
+}
+
+__device__ __forceinline__ void fill_exptab(TpShared& sh) {
+  if (threadIdx.x < 64) sh.exptab[threadIdx.x] = exp2(static_cast<double>(threadIdx.x) * (1.0 / 64.0));
+}
+
+__global__ __launch_bounds__(kTpBlock) void topp_locate_kernel(RowArgs a) {
+  __shared__ TpShared sh;
+  const int64_t r = blockIdx.x;
+  if (r >= a.n_rows) return;
+  TpRowWs& w = row_ws(a, r);
+  const float T = a.temperature[r], P = a.top_p[r], A0 = w.row.A0;
+  const float c = temperature_ok(T) ? kLog2e / T : kLog2e;
+  const bool anchored = P > 0.0f && P < 1.0f && temperature_ok(T) && A0 > -INFINITY && A0 < INFINITY;
+  if (threadIdx.x < kWave) {
+    const Partial p = merge_waves(w.part[threadIdx.x % kParts].p, kParts, c);
+    if (threadIdx.x == 0) {
+      sh.p = p;
+      sh.active = P > 0.0f && P < 1.0f && temperature_ok(T) &&
+                  (row_flags(a, r, p, T) & (PR_FLAG_NONFINITE | PR_FLAG_BAD_TP)) == 0;
+    }
+  }
+  fill_exptab(sh);
+  uint32_t n_above = 0;
+  if (anchored) {
+    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+    constexpr int kVecs = kHB / 2 / kTpBlock;
+    u64x2 x[kParts][kVecs];
+#pragma unroll
+    for (int g = 0; g < kParts; ++g)
+#pragma unroll
+      for (int k = 0; k < kVecs; ++k)
+        x[g][k] = reinterpret_cast<const u64x2*>(w.part[g].bins)[threadIdx.x + k * kTpBlock];
+#pragma unroll
+    for (int k = 0; k < kVecs; ++k) {
+      u64x2 t = x[0][k];
+#pragma unroll
+      for (int g = 1; g < kParts; ++g) t += x[g][k];
+      reinterpret_cast<u64x2*>(sh.u.hs.bins)[threadIdx.x + k * kTpBlock] = t;
+    }
+    for (int g = 0; g < kParts; ++g) {
+      const uint32_t n = w.part[g].n_above;
+      if (threadIdx.x < n && n_above + threadIdx.x < static_cast<uint32_t>(kAboveCap) &&
+          threadIdx.x < static_cast<uint32_t>(kAboveCap))
+        sh.above[n_above + threadIdx.x] = w.part[g].above[threadIdx.x];
+      n_above += n;
+    }
+  }
+  if (threadIdx.x == 0) sh.n_above = n_above;
+  __syncthreads();
+  const Partial p = sh.p;
+  int32_t state = kRowPlain;
+  Window W{};
+  if (sh.active) {
+    HistHook hk;
+    set_hook(hk, sh, T, A0, anchored);
+    uint32_t n_full;
+    state = anchored && locate_window(row_dist(p, T), P, hk, sh, W, n_full, [](const Window&) { return false; })
+                ? kRowSplit
+                : kRowThreePass;
+  }
+  if (threadIdx.x == 0) {
+    w.row.p = p;
+    w.row.W = W;
+    w.row.state = state;
+    w.row.wcount = 0;
+  }
+}
+
+template <typename Tin>
+__global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) void topp_sum_kernel(RowArgs a) {
+  __shared__ TpShared sh;
+  const int64_t r = blockIdx.x / kParts;
+  const int g = blockIdx.x % kParts;
+  if (r >= a.n_rows) return;
+  TpRowWs& w = row_ws(a, r);
+  const TpRowState st = w.row;
+  if (st.state != kRowSplit) return;
+  constexpr int VEC = Elem<Tin>::kVec;
+  const void* row = static_cast<const Tin*>(a.logits) + r * a.row_stride;
+  const int64_t h = head_elems<Tin>(row, a.V);
+  const int64_t nvec = (a.V - h) / VEC;
+  const int64_t vb = nvec * g / kParts, ve = nvec * (g + 1) / kParts;
+  constexpr int LD = 2;
+  vec4u v[LD];
+  stretch_prefetch<Tin, kTpBlock, LD>(row, h, vb, ve, v);
+  const float T = a.temperature[r];
+  const Dist D = row_dist(st.p, T);
+  HistHook hk;
+  set_hook(hk, sh, T, st.A0, true);
+  fill_exptab(sh);
+  if (threadIdx.x == 0) sh.wcount = 0;
+  __syncthreads();
+  const double* tab = sh.exptab;
+  const int b_lo = st.W.b_lo, b_hi = st.W.b_hi;
+  double sT = 0.0, mA = 0.0, eA = 0.0;
+  auto visit = [&](float z) {
+    const float x = fmaf(z, hk.kz4, hk.k04);
+    if (!(x < static_cast<float>(kHB) * kOffQ)) return;  // the binned logits, as in the exact pass
+    const double dd = D.d64(z);
+    const double e = exp_tang(fmax(dd, -700.0), tab);
+    sT += e;
+    const int b = x >= 0.0f ? static_cast<int>(static_cast<uint32_t>(x) >> kOffBits) : -1;
+    if (b < b_lo) {
+      mA += e;
+      eA = fma(e, dd, eA);
+    } else if (b <= b_hi) {
+      const uint32_t slot = atomicAdd(&sh.wcount, 1u);
+      if (slot < static_cast<uint32_t>(kCap)) sh.win[slot] = z;
+    }
+  };
+  const int t = threadIdx.x;
+  if (g == 0 && t < h) visit(Elem<Tin>::load1(row, t));
+  const vec4u* vp = reinterpret_cast<const vec4u*>(static_cast<const Tin*>(row) + h);
+  stream_stretch<Tin, kTpBlock, 1, LD>(vp, vb, ve, v, [&](const vec4u* vv, int64_t) {
+    float z[VEC];
+    Elem<Tin>::unpack(vv[0], z);
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) visit(z[k]);
+  });
+  if (g == kParts - 1)
+    for (int64_t e = h + nvec * VEC + t; e < a.V; e += kTpBlock) visit(Elem<Tin>::load1(row, e));
+  double unused = 0.0;
+  block_sum2(mA, eA, sh);
+  block_sum2(sT, unused, sh);
+  // The part's window logits: the window as a whole holds st.W.inwin <= kCap
+  // of them, so a part's fit its LDS and all parts' the row's list. (Their
+  // order there varies; the cut sorts them.)
+  const uint32_t n = min(sh.wcount, static_cast<uint32_t>(kCap));
+  if (t == 0) {
+    w.part[g].mA = mA;
+    w.part[g].eA = eA;
+    w.part[g].sT = sT;
+    if (n > 0) sh.b_lo = atomicAdd(&w.row.wcount, n);
+  }
+  __syncthreads();
+  for (uint32_t i = t; i < n; i += kTpBlock)
+    if (sh.b_lo + i < static_cast<uint32_t>(kCap)) w.win[sh.b_lo + i] = sh.win[i];
+}
+
+template <typename Tin>
+__global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) void topp_cut_kernel(RowArgs a) {
+  __shared__ TpShared sh;
+  const int64_t r = blockIdx.x;
+  if (r >= a.n_rows) return;
+  TpRowWs& w = row_ws(a, r);
+  const TpRowState st = w.row;
+  const void* row = static_cast<const Tin*>(a.logits) + r * a.row_stride;
+  const RowCtx cx = row_ctx<Tin>(a, r, row);
+  if (st.state == kRowPlain) {
+    finish_row(a, r, st.p, cx, st.fix, nullptr);
+    return;
+  }
+  const float P = a.top_p[r];
+  const Dist D = row_dist(st.p, cx.T);
+  Nucleus nuc;
+  bool ok = false;
+  if (st.state == kRowSplit && st.wcount <= static_cast<uint32_t>(kCap)) {
+    double mA = 0.0, eA = 0.0, sT = 0.0;
+    for (int g = 0; g < kParts; ++g) {
+      mA += w.part[g].mA;
+      eA += w.part[g].eA;
+      sT += w.part[g].sT;
+    }
+    for (uint32_t i = threadIdx.x; i < st.wcount; i += kTpBlock) sh.win[i] = w.win[i];
+    fill_exptab(sh);
+    __syncthreads();
+    const double target = static_cast<double>(P) * sT;
+    ok = cut_window(
+        sh, st.wcount, st.W.above, mA, eA, [&](float z) { return D.d64(z); },
+        [&](double, double& t_lo, double& t_hi) { t_lo = t_hi = target; }, nuc);
+  }
+  if (!ok) {
+    __syncthreads();
+    const int64_t h = head_elems<Tin>(row, a.V);
+    nuc = legacy_nucleus<Tin>(row, a.V, h, (a.V - h) / Elem<Tin>::kVec, D, P, sh);
+  }
+  finish_row(a, r, st.p, cx, st.fix, &nuc);
+}
+
+// The batches whose rows are spread, at the price of three more launches and
+// of 32 KB of histogram written and read per part. One workgroup per row
+// against eight, us: V = 151,936 bf16 1 row 58 / 39, 16 rows 94 / 52, 64 rows
+// 112 / 71, 128 rows 118 / 97, 200 rows 133 / 138; V = 262,144 f32 16 rows 146 /
+// 52, 128 rows 185 / 110; V = 65,536 16 rows 54 / 40 (bf16), 61 / 40 (f32), but
+// 128 rows 62 / 64; V = 50,257 64 rows 47 / 51; V = 32,000 16 rows 36 / 39.
+size_t topp_split_workspace(int64_t n_rows, int32_t V) {
+  const int64_t most = V >= 131072 ? 128 : (V >= 65536 ? 32 : 0);
+  return n_rows > 0 && n_rows <= most ? static_cast<size_t>(n_rows) * sizeof(TpRowWs) : 0;
+}
+
+// (A streaming state keeps room for steps of up to 64 rows, 19 MB.)
+size_t topp_split_workspace_most(int64_t n_rows) {
+  return topp_split_workspace(n_rows < 64 ? n_rows : 64, std::numeric_limits<int32_t>::max());
+}
+
+template <typename Tin>
+static hipError_t launch_topp_split(const RowArgs& a, hipStream_t stream) {
+  const unsigned n = static_cast<unsigned>(a.n_rows);
+  topp_scan_kernel<Tin><<<n * kParts, kTpBlock, 0, stream>>>(a);
+  topp_locate_kernel<<<n, kTpBlock, 0, stream>>>(a);
+  topp_sum_kernel<Tin><<<n * kParts, kTpBlock, 0, stream>>>(a);
+  topp_cut_kernel<Tin><<<n, kTpBlock, 0, stream>>>(a);
+  return hipGetLastError();
+}
+
 size_t topp_workspace(pr_dtype, int64_t, int32_t) { return 0; }
 
-hipError_t launch_topp(const RowArgs& a, pr_dtype dtype, void*, hipStream_t stream) {
-  if (a.n_rows == 0) return hipSuccess;
+hipError_t launch_topp(const RowArgs& args, pr_dtype dtype, void* workspace, size_t workspace_bytes,
+                       hipStream_t stream) {
+  if (args.n_rows == 0) return hipSuccess;
+  RowArgs a = args;
   const dim3 grid(static_cast<unsigned>(a.n_rows));
   const bool seq = a.X != nullptr;
+  const size_t split = topp_split_workspace(a.n_rows, a.V);
+  if (!seq && split > 0 && workspace && workspace_bytes >= split) {
+    a.ws = static_cast<Partial*>(workspace);
+    return dtype == PR_BF16 ? launch_topp_split<uint16_t>(a, stream) : launch_topp_split<float>(a, stream);
+  }
   if (dtype == PR_BF16) {
     if (seq)
       topp_kernel<uint16_t, true><<<grid, kTpBlock, 0, stream>>>(a);

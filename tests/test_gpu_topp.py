@@ -280,3 +280,74 @@ def test_hardware_exp2_bound():
     e1 = float(w[:1].view(np.float64)[0])
     x1 = float(np.array([w[1]], dtype=np.int64).astype(np.uint32).view(np.float32)[0])
     assert -1.0 <= x1 <= 1.0 and 0.0 < e1 <= err
+
+
+@pytest.mark.parametrize("dtype,V,offset", [(torch.float32, 65536, 0), (torch.float32, 65543, 1),
+                                            (torch.bfloat16, 65536, 0), (torch.bfloat16, 70001, 3)])
+def test_topp_rows_over_several_workgroups(monkeypatch, dtype, V, offset):
+    """Small batches of long rows, each over eight workgroups: every kind of
+    row (flat, peaked, ties over the boundary, heavy ties, a distant maximum
+    beyond the anchor's range, large |z| / T, masked logits, no nucleus,
+    undefined, the sampled token outside), aligned and not, against the
+    oracle; the same rows with one workgroup each agree in every whole
+    number, and a second run is bit-identical."""
+    rng = np.random.default_rng(V)
+    n = 18
+    s = np.concatenate([np.linspace(0.2, 6.0, 8), np.full(n - 8, 1.0)])[:, None]
+    z = rng.normal(0, 1, (n, V)) * s
+    z[np.arange(8), rng.integers(0, V, 8)] += rng.uniform(0, 15, 8)
+    z[8] = 0.5                                   # every logit tied
+    z[9] = np.round(z[9] * 4) / 4                # blocks of ties
+    z[10, V - 1] = 120.0                         # far above the anchor
+    z[11] += 6000.0                              # beyond the bins' accuracy
+    z[12, rng.permutation(V)[:V // 2]] = -np.inf
+    z[13, 7] = np.nan
+    z[14] = -np.inf
+    z[14, 9] = 1.0                               # one token
+    z[15, V - 700:] += 40.0                      # more logits above the bins than the list holds
+    ids = rng.integers(0, V, n)
+    ids[:8:2] = np.argmax(z[:8:2], axis=1)
+    T = rng.uniform(0.3, 1.2, n)
+    P = rng.uniform(0.5, 0.98, n)
+    P[16], T[17] = 1.0, -1.0
+    wide = np.zeros((n, V + offset))
+    wide[:, offset:] = z
+    logits, ids, T, P = _run(wide, ids, T, P, dtype)
+    logits = logits[:, offset:]
+    print(f"case topp several workgroups V={V} offset={offset} {dtype}", flush=True)
+    L = pr._abi.lib()
+    assert L.pr_token_features_workspace_full(pr._dtype_code(logits), n, V, 1) > 0
+    got = gpu_features(logits, ids, T, P)
+    again = gpu_features(logits, ids, T, P)
+    with monkeypatch.context() as m:
+        m.setattr(L, "pr_token_features_workspace_full", lambda *a: 0)
+        one = gpu_features(logits, ids, T, P)
+    for k in got:
+        assert np.array_equal(got[k].view(np.int32), again[k].view(np.int32)), k
+    for k in ("rank", "argmax", "cutoff", "flags"):
+        assert np.array_equal(got[k], one[k]), k
+    ref = oracle_features(logits, ids, T, P)
+    compare_features(got, ref)
+    compare_features(one, ref)
+
+
+def test_topp_row_and_vocabulary_limits():
+    """Either side of the batch sizes and vocabularies that spread their rows,
+    at the workspace's exact size (nothing past it is written)."""
+    L = pr._abi.lib()
+    for dtype, n, V in ((torch.bfloat16, 32, 65536), (torch.bfloat16, 33, 65536), (torch.bfloat16, 2, 65535),
+                        (torch.float32, 1, 131072), (torch.bfloat16, 128, 131072), (torch.bfloat16, 129, 131072)):
+        full = int(L.pr_token_features_workspace_full(1 if dtype == torch.bfloat16 else 0, n, V, 1))
+        assert (full > 0) == (n <= (128 if V >= 131072 else 32) and V >= 65536)
+        g = torch.Generator(device="cuda").manual_seed(n)
+        z = (torch.randn((n, V), generator=g, device="cuda") * 2.5).to(dtype)
+        ids = torch.argmax(z.float(), 1).to(torch.int32)
+        T, P = torch.full((n,), 0.8, device="cuda"), torch.full((n,), 0.9, device="cuda")
+        buf = torch.full((full + 4096,), 0x7F, dtype=torch.uint8, device="cuda")
+        print(f"case topp limits n={n} V={V} {dtype}", flush=True)
+        f = pr.token_features(z, ids, T, P, workspace=buf[:max(full, 1)])
+        torch.cuda.synchronize()
+        assert bool((buf[full:] == 0x7F).all())
+        rows = [0, n - 1]
+        o = oracle_features(z, ids, T, P, rows)
+        compare_features({k: v.cpu().numpy() for k, v in f.items()}, o, rows)
