@@ -192,7 +192,8 @@ pr_status pr_token_features_noalloc(const void* logits, pr_dtype dtype, int64_t 
 }
 
 size_t pr_feature_sequence_workspace(pr_dtype dtype, int64_t n_rows, int32_t vocab, int32_t top_p_on) {
-  return top_p_on || vocab < 2 ? 0 : lane_workspace_bytes(n_rows, vocab, dtype, true, false);
+  if (vocab < 2) return 0;
+  return top_p_on ? topp_split_workspace(n_rows, vocab) : lane_workspace_bytes(n_rows, vocab, dtype, true, false);
 }
 
 pr_status pr_feature_sequence(const void* logits, pr_dtype dtype, int64_t n_rows, int32_t vocab,
@@ -230,7 +231,7 @@ pr_status pr_feature_sequence_ws(const void* logits, pr_dtype dtype, int64_t n_r
   a.top_k = top_k;
   if (top_p && vocab >= kTopPMaxVocab) return PR_ERR_UNSUPPORTED;
   if (workspace && !aligned(workspace, 16)) return PR_ERR_INVALID_ARG;
-  if (top_p) return hip_status(launch_topp(a, dtype, nullptr, 0, as_stream(stream)));
+  if (top_p) return hip_status(launch_topp(a, dtype, workspace, workspace_bytes, as_stream(stream)));
   const size_t need = lane_workspace_bytes(n_rows, vocab, dtype, true, false);
   if (workspace && need > 0 && workspace_bytes >= need) {
     a.G = lane_split(n_rows, vocab, dtype);

@@ -224,10 +224,11 @@ __device__ __forceinline__ uint32_t compact(const Lds& s, uint32_t n, uint32_t k
 // [vb, ve) of the row's nvec aligned vectors, h scalar head logits, the tail
 // after them), written to s.top in descending order (-inf where the row has
 // fewer than K logits). hk is the lane's hook after the scan; U vectors per
-// step. Every thread of the workgroup calls it.
+// step; head, tail: whether the scan took the scalar logits before and after
+// the vectors. Every thread of the workgroup calls it.
 template <typename Tin, int BLOCK, int U>
 __device__ void select_topk(const void* row, int32_t V, int64_t h, int64_t vb, int64_t ve, int64_t nvec, int K,
-                            const Hook& hk, const Lds& s) {
+                            const Hook& hk, const Lds& s, bool head = true, bool tail = true) {
   constexpr int VEC = Elem<Tin>::kVec;
   constexpr int PASSES = sizeof(Tin) == 2 ? 2 : 4;
   constexpr int NW = BLOCK / kWave;
@@ -354,8 +355,8 @@ __device__ void select_topk(const void* row, int32_t V, int64_t h, int64_t vb, i
         // the lane's scalar head and tail logits
         float zh = -INFINITY, zt = -INFINITY;
         if (t == 0) {
-          if (tf < h) zh = Elem<Tin>::load1(row, tf);
-          if (tail0 + tf < V) zt = Elem<Tin>::load1(row, tail0 + tf);
+          if (head && tf < h) zh = Elem<Tin>::load1(row, tf);
+          if (tail && tail0 + tf < V) zt = Elem<Tin>::load1(row, tail0 + tf);
         }
         add(zh, tf);
         add(zt, tf);

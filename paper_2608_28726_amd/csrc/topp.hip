@@ -1475,6 +1475,34 @@ __device__ __forceinline__ void finish_row(const RowArgs& a, int64_t r, const Pa
   if (pm.slot >= 0) p2::feed_row(a, pm, conf);
 }
 
+// The same for the sequence variant, with sh.topk: row r of X, the top-K
+// probabilities taken on the renormalised nucleus. The waves that have nothing
+// to do leave early for f32 and pass over the block for bf16: the row kernel
+// sits at its register limit, and of the two forms one keeps a pointer of its
+// inner loops in scratch memory, another one for each type (bf16 1,000 rows x
+// 151,936: 276 us, 322 us the other way; f32 4,096 rows x 262,144: 1,255 us,
+// 1,319 us the other way).
+template <typename Tin>
+__device__ __forceinline__ void finish_sequence_row(const RowArgs& a, int64_t r, const Partial& p, const RowCtx& cx,
+                                                    uint32_t fix, const Nucleus* nuc, const TpShared& sh) {
+  if (sizeof(Tin) == 4 && threadIdx.x >= kWave) return;
+  if (threadIdx.x < kWave) {
+    float H;
+    if (nuc) {
+      const int j = a.top_k < nuc->k ? a.top_k : nuc->k;  // the nucleus may hold fewer than K tokens
+      H = topk::topk_entropy_f64(sh.topk, j, p.m, cx.T, nuc->S);
+    } else {
+      H = topk::topk_entropy_f32(sh.topk, a.top_k, p.m, cx.c, p.S);
+    }
+    const float rho = topk::position_fraction(a.offsets, a.n_req, r);
+    if (threadIdx.x == 0) {
+      float conf[4];
+      const uint32_t flags = finalize_row(a, r, p, cx, fix, conf, nuc);
+      write_sequence_row(a, r, conf, flags, H, rho);
+    }
+  }
+}
+
 // SEQ: also the row's K largest logits (found in the stats pass) and row r
 // of the verifier input sequence X, with the top-K probabilities taken on the
 // renormalised nucleus.
@@ -1555,15 +1583,7 @@ __global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) v
   p = sh.p;
   if (!sh.active) {
     if constexpr (SEQ) {
-      if (threadIdx.x < kWave) {
-        const float H = topk::topk_entropy_f32(sh.topk, a.top_k, p.m, cx.c, p.S);
-        const float rho = topk::position_fraction(a.offsets, a.n_req, r);
-        if (threadIdx.x == 0) {
-          float conf[4];
-          const uint32_t flags = finalize_row(a, r, p, cx, fix, conf);
-          write_sequence_row(a, r, conf, flags, H, rho);
-        }
-      }
+      finish_sequence_row<Tin>(a, r, p, cx, fix, nullptr, sh);
       return;
     }
     finish_row(a, r, p, cx, fix, nullptr);
@@ -1580,16 +1600,7 @@ __global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) v
   if (!(anchored && hist_nucleus<Tin>(row, a.V, cx.h, nvec, D, P, A0, hk, hp.b, sh, nuc)))
     nuc = legacy_nucleus<Tin>(row, a.V, cx.h, nvec, D, P, sh);
   if constexpr (SEQ) {
-    if (threadIdx.x < kWave) {
-      const int j = a.top_k < nuc.k ? a.top_k : nuc.k;  // the nucleus may hold fewer than K tokens
-      const float H = topk::topk_entropy_f64(sh.topk, j, p.m, T, nuc.S);
-      const float rho = topk::position_fraction(a.offsets, a.n_req, r);
-      if (threadIdx.x == 0) {
-        float conf[4];
-        const uint32_t flags = finalize_row(a, r, p, cx, fix, conf, &nuc);
-        write_sequence_row(a, r, conf, flags, H, rho);
-      }
-    }
+    finish_sequence_row<Tin>(a, r, p, cx, fix, &nuc, sh);
     return;
   }
   finish_row(a, r, p, cx, fix, &nuc);
@@ -1621,6 +1632,7 @@ struct TpRowState {  // a row between the kernels
 struct TpPart {  // one part of a row
   uint64_t bins[kHB];
   float above[kAboveCap];
+  float top[topk::kMaxK];  // the part's K largest logits (sequence variant)
   Partial p;
   double sT, mA, eA;
   uint32_t n_above, fix;
@@ -1655,7 +1667,27 @@ __device__ __forceinline__ float row_anchor(const void* row, int64_t h, int64_t 
   return m;
 }
 
-template <typename Tin>
+// The row's K largest logits, descending, into sh.topk: the K largest of its
+// parts' (ties by part and place), each ranked by counting.
+__device__ __forceinline__ void merge_topk(const TpRowWs& w, int K, TpShared& sh) {
+  constexpr int n = kParts * topk::kMaxK;
+  static_assert(n <= kTpBlock, "one value per thread");
+  const int t = threadIdx.x, k = t % topk::kMaxK;
+  const bool mine = t < n && k < K;
+  const float v = mine ? w.part[t / topk::kMaxK].top[k] : 0.0f;
+  const uint32_t key = mine ? max(float_key(v), 1u) : 0u;  // above the places that hold nothing
+  uint32_t* keys = reinterpret_cast<uint32_t*>(sh.win);
+  if (t < n) keys[t] = key;
+  __syncthreads();
+  if (mine) {
+    int rank = 0;
+    for (int q = 0; q < n; ++q) rank += (keys[q] > key || (keys[q] == key && q < t)) ? 1 : 0;
+    if (rank < K) sh.topk[rank] = v;
+  }
+  __syncthreads();
+}
+
+template <typename Tin, bool SEQ>
 __global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) void topp_scan_kernel(RowArgs a) {
   __shared__ TpShared sh;
   const int64_t r = blockIdx.x / kParts;
@@ -1676,17 +1708,18 @@ __global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) v
   const float P = a.top_p[r];
   const bool nucleus_row = P > 0.0f && P < 1.0f && temperature_ok(cx.T);
   const bool anchored = nucleus_row && A0 > -INFINITY && A0 < INFINITY;
-  HistHook hk;
-  set_hook(hk, sh, cx.T, A0, anchored);
+  using TopkHook = typename std::conditional<SEQ, topk::Hook, NoHook>::type;
+  HookPair<HistHook, TopkHook> hp;
+  set_hook(hp.a, sh, cx.T, A0, anchored);
+  if constexpr (SEQ) hp.b.init();
   Lane L;
   lane_init(L);
   if (nucleus_row) {
     [[clang::always_inline]] scan_stretch<Tin, kTpBlock, 2, kLD, false, false>(row, a.V, vb, ve, g == 0,
-                                                                               g == kParts - 1, nvec, cx, L, v, hk);
+                                                                               g == kParts - 1, nvec, cx, L, v, hp);
   } else {
     [[clang::always_inline]] scan_stretch<Tin, kTpBlock, 2, kLD, false, true>(row, a.V, vb, ve, g == 0,
-                                                                              g == kParts - 1, nvec, cx, L, v,
-                                                                              NoHook());
+                                                                              g == kParts - 1, nvec, cx, L, v, hp.b);
   }
   const Partial p = block_merge<kTpBlock>(L, cx.c);  // its barrier also ends the counting
   TpRowWs& w = row_ws(a, r);
@@ -1701,6 +1734,11 @@ __global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) v
   if (threadIdx.x == 0) {
     o.p = p;
     o.n_above = sh.n_above;
+  }
+  if constexpr (SEQ) {
+    [[clang::always_inline]] topk::select_topk<Tin, kTpBlock, 2>(row, a.V, cx.h, vb, ve, nvec, a.top_k, hp.b,
+                                                                 topk_lds(sh), g == 0, g == kParts - 1);
+    if (threadIdx.x < static_cast<unsigned>(a.top_k)) o.top[threadIdx.x] = sh.topk[threadIdx.x];
   }
   if (!anchored) return;
   typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
@@ -1857,7 +1895,7 @@ __global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) v
     if (sh.b_lo + i < static_cast<uint32_t>(kCap)) w.win[sh.b_lo + i] = sh.win[i];
 }
 
-template <typename Tin>
+template <typename Tin, bool SEQ>
 __global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) void topp_cut_kernel(RowArgs a) {
   __shared__ TpShared sh;
   const int64_t r = blockIdx.x;
@@ -1866,8 +1904,10 @@ __global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) v
   const TpRowState st = w.row;
   const void* row = static_cast<const Tin*>(a.logits) + r * a.row_stride;
   const RowCtx cx = row_ctx<Tin>(a, r, row);
+  if constexpr (SEQ) merge_topk(w, a.top_k, sh);
   if (st.state == kRowPlain) {
-    finish_row(a, r, st.p, cx, st.fix, nullptr);
+    if constexpr (SEQ) finish_sequence_row<Tin>(a, r, st.p, cx, st.fix, nullptr, sh);
+    else finish_row(a, r, st.p, cx, st.fix, nullptr);
     return;
   }
   const float P = a.top_p[r];
@@ -1894,7 +1934,8 @@ __global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) v
     const int64_t h = head_elems<Tin>(row, a.V);
     nuc = legacy_nucleus<Tin>(row, a.V, h, (a.V - h) / Elem<Tin>::kVec, D, P, sh);
   }
-  finish_row(a, r, st.p, cx, st.fix, &nuc);
+  if constexpr (SEQ) finish_sequence_row<Tin>(a, r, st.p, cx, st.fix, &nuc, sh);
+  else finish_row(a, r, st.p, cx, st.fix, &nuc);
 }
 
 // The batches whose rows are spread, at the price of three more launches and
@@ -1902,7 +1943,11 @@ __global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) v
 // against eight, us: V = 151,936 bf16 1 row 58 / 39, 16 rows 94 / 52, 64 rows
 // 112 / 71, 128 rows 118 / 97, 200 rows 133 / 138; V = 262,144 f32 16 rows 146 /
 // 52, 128 rows 185 / 110; V = 65,536 16 rows 54 / 40 (bf16), 61 / 40 (f32), but
-// 128 rows 62 / 64; V = 50,257 64 rows 47 / 51; V = 32,000 16 rows 36 / 39.
+// 128 rows 62 / 64; V = 50,257 64 rows 47 / 51; V = 32,000 16 rows 36 / 39. The
+// sequence variant: V = 151,936 bf16 1 row 64 / 54, 16 rows 101 / 67, 64 rows
+// 118 / 85, 128 rows 126 / 119; V = 262,144 f32 64 rows 174 / 90, 128 rows 188 /
+// 135; V = 131,072 128 rows 129 / 103 (bf16), 126 / 109 (f32); V = 65,536 32 rows
+// 63 / 55 (bf16), 61 / 58 (f32).
 size_t topp_split_workspace(int64_t n_rows, int32_t V) {
   const int64_t most = V >= 131072 ? 128 : (V >= 65536 ? 32 : 0);
   return n_rows > 0 && n_rows <= most ? static_cast<size_t>(n_rows) * sizeof(TpRowWs) : 0;
@@ -1913,13 +1958,13 @@ size_t topp_split_workspace_most(int64_t n_rows) {
   return topp_split_workspace(n_rows < 64 ? n_rows : 64, std::numeric_limits<int32_t>::max());
 }
 
-template <typename Tin>
+template <typename Tin, bool SEQ>
 static hipError_t launch_topp_split(const RowArgs& a, hipStream_t stream) {
   const unsigned n = static_cast<unsigned>(a.n_rows);
-  topp_scan_kernel<Tin><<<n * kParts, kTpBlock, 0, stream>>>(a);
+  topp_scan_kernel<Tin, SEQ><<<n * kParts, kTpBlock, 0, stream>>>(a);
   topp_locate_kernel<<<n, kTpBlock, 0, stream>>>(a);
   topp_sum_kernel<Tin><<<n * kParts, kTpBlock, 0, stream>>>(a);
-  topp_cut_kernel<Tin><<<n, kTpBlock, 0, stream>>>(a);
+  topp_cut_kernel<Tin, SEQ><<<n, kTpBlock, 0, stream>>>(a);
   return hipGetLastError();
 }
 
@@ -1932,9 +1977,11 @@ hipError_t launch_topp(const RowArgs& args, pr_dtype dtype, void* workspace, siz
   const dim3 grid(static_cast<unsigned>(a.n_rows));
   const bool seq = a.X != nullptr;
   const size_t split = topp_split_workspace(a.n_rows, a.V);
-  if (!seq && split > 0 && workspace && workspace_bytes >= split) {
+  if (split > 0 && workspace && workspace_bytes >= split) {
     a.ws = static_cast<Partial*>(workspace);
-    return dtype == PR_BF16 ? launch_topp_split<uint16_t>(a, stream) : launch_topp_split<float>(a, stream);
+    if (dtype == PR_BF16)
+      return seq ? launch_topp_split<uint16_t, true>(a, stream) : launch_topp_split<uint16_t, false>(a, stream);
+    return seq ? launch_topp_split<float, true>(a, stream) : launch_topp_split<float, false>(a, stream);
   }
   if (dtype == PR_BF16) {
     if (seq)

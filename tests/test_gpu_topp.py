@@ -9,7 +9,9 @@ import torch
 
 import paper_2608_28726_amd as pr
 from paper_2608_28726_amd import workloads as wl
+from oracle import sequence as oseq
 from tests.gpu_common import compare_features, gpu_features, oracle_features, require_gpu, to_dev
+from tests.helpers import assert_floats
 
 pytestmark = pytest.mark.gpu
 
@@ -329,6 +331,23 @@ def test_topp_rows_over_several_workgroups(monkeypatch, dtype, V, offset):
     ref = oracle_features(logits, ids, T, P)
     compare_features(got, ref)
     compare_features(one, ref)
+    # the verifier input sequence: the K largest logits come from all parts
+    off = torch.tensor([0, 5, n], dtype=torch.int32, device="cuda")
+    for K in (1, 20, 32):
+        X, f = pr.feature_sequence(logits, ids, T, off, top_p=P, top_k=K, features=True)
+        with monkeypatch.context() as m:
+            m.setattr(L, "pr_feature_sequence_workspace", lambda *a: 0)
+            X1 = pr.feature_sequence(logits, ids, T, off, top_p=P, top_k=K)
+        torch.cuda.synchronize()
+        H = oseq.topk_entropy_batch(wl.to_host_raw(logits), "f32" if dtype == torch.float32 else "bf16",
+                                    T.cpu().numpy(), P.cpu().numpy(), K)
+        Xo = oseq.feature_sequence(ref, H, off.cpu().numpy())
+        sure = ~ref["ambiguous"]
+        for c in range(4):
+            assert_floats(f"X[{c}] K={K}", X[:, c].cpu().numpy(), Xo[:, c], mask=sure)
+            assert_floats(f"X[{c}] K={K}, one workgroup", X1[:, c].cpu().numpy(), Xo[:, c], mask=sure)
+        for k in got:
+            assert np.array_equal(f[k].cpu().numpy().view(np.int32), got[k].view(np.int32)), k
 
 
 def test_topp_row_and_vocabulary_limits():
