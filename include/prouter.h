@@ -388,7 +388,9 @@ typedef struct pr_stream pr_stream;
  * Chlamtac, CACM 1985), 224 bytes per slot, any number of tokens per
  * request. Its estimate is exact up to 5 tokens; an infinite value of a
  * column (a margin of +inf, a log-prob of -inf) makes that column's
- * quantile NaN for the request (the mean and minimum keep it).
+ * quantile NaN for the request (the mean and minimum keep it). Besides the
+ * slots' state it holds 297 KB per slot, for at most 64 slots, in which top-p
+ * steps spread few rows over the device.
  */
 pr_status pr_stream_create(int32_t max_slots, int32_t max_len, const pr_agg_params* params, pr_stream** state);
 
