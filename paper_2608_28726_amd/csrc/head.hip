@@ -494,7 +494,11 @@ struct Queries {
 // a score exceeds it by more than kSlack (the masses stay below 2^kSlack, in
 // float32 a change of exponent only). The products start from -m, so that in
 // all but the first tiles the update is an exp and an add per score; the
-// query's sum over its four lanes is taken once at the end.
+// query's sum over its four lanes is taken once at the end. Each query's
+// reference moves by its own scores alone (a wave enters the step for all its
+// queries as soon as one needs it, and the others move by 0): a move by a
+// fraction of an octave changes the rounding of what follows, and the result of
+// a query must not depend on the queries beside it.
 constexpr float kSlack = 8.0f;
 
 __device__ __forceinline__ void attend(const __bf16* Kh, const float* Vh, int64_t first, int64_t last, int64_t lo,
@@ -549,11 +553,11 @@ __device__ __forceinline__ void attend(const __bf16* Kh, const float* Vh, int64_
 #pragma unroll
       for (int r = 0; r < 4; ++r) tm = fmaxf(tm, s[j][r]);
     if (t == first || __any(tm > kSlack)) {
-      // the reference moves to the largest score so far (from 0 to the first
-      // tile's, which may lie below)
+      // the reference of a query that needs it moves to its largest score so
+      // far (from 0 to the first tile's, which may lie below)
       tm = fmaxf(tm, __shfl_xor(tm, 16));
       tm = fmaxf(tm, __shfl_xor(tm, 32));
-      const float d = t == first ? tm : fmaxf(tm, 0.0f);
+      const float d = t == first || tm > kSlack ? tm : 0.0f;
       const float corr = fast_exp2(-d);
       st.l = t == first ? 0.0f : st.l * corr;
       st.o = t == first ? f4{0.0f, 0.0f, 0.0f, 0.0f} : st.o * corr;
@@ -632,10 +636,15 @@ __global__ __launch_bounds__(kThreads) void head_layer_kernel(HeadArgs a, int la
   const float* Wl = a.weights + at;
   const __bf16* Ws = a.Ws + 3 * at;
   Attn st;
+  // Q and H have one buffer: in this launch the workgroups of the neighbouring
+  // requests write the next layer's into their rows, and rows past the last
+  // group hold whatever the workspace held. In the place of a block's rows that
+  // are not its request's (computed and never written) the nearest of the
+  // request's is read.
+  const int64_t own = min(max(r0 + i16, lo), hi - 1);
   {
-    Queries q;  // rows that are not the request's are read and never written
-    const int64_t row = r0 + i16;
-    const __bf16* Q = a.Q + group_of(a, hd, row) * kQK + 128 * (g % 2) + 8 * (row & 15);
+    Queries q;
+    const __bf16* Q = a.Q + group_of(a, hd, own) * kQK + 128 * (g % 2) + 8 * (own & 15);
     q.q11 = *reinterpret_cast<const b8*>(Q);
     q.q22 = *reinterpret_cast<const b8*>(Q + 256);
     q.q31 = *reinterpret_cast<const b8*>(Q + (g < 2 ? 512 : 0));
@@ -651,7 +660,7 @@ __global__ __launch_bounds__(kThreads) void head_layer_kernel(HeadArgs a, int la
   if (half == 0) {
     wo.load(Ws + 3 * kW_o, hd);
     bo = *reinterpret_cast<const f4*>(Wl + kB_o + 16 * hd + 4 * g);
-    hres = *reinterpret_cast<const f4*>(a.H + (r0 + i16) * D + 16 * hd + 4 * g);
+    hres = *reinterpret_cast<const f4*>(a.H + own * D + 16 * hd + 4 * g);
   }
   const int lr = threadIdx.x / kTPR, lc = (threadIdx.x % kTPR) * 4;  // LayerNorm: row and first column
   const f4 g1 = *reinterpret_cast<const f4*>(Wl + kLn1g + lc), e1 = *reinterpret_cast<const f4*>(Wl + kLn1b + lc);

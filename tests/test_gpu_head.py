@@ -183,3 +183,39 @@ def test_scaled_weights():
     got = run_head(X, off, weights, max_len=333)
     ref = ohead.head_scores(X.astype(np.float64), off, weights.astype(np.float64))
     assert_floats("head score (sharp attention)", got, ref)
+
+
+@pytest.mark.parametrize("full", [True, False])
+@pytest.mark.parametrize("scale", [4.0, 12.0])
+def test_score_depends_on_its_request_alone(scale, full):
+    """Sharp attention on requests that start inside row groups and are longer
+    than two key tiles: a score is the same to the bit whatever the workspace
+    held before, whatever its neighbours hold, and run after run."""
+    lengths = [37, 200, 131, 5, 261, 66, 333, 2, 150, 47]
+    X, off = synthetic_sequence(lengths, 51)
+    other, _ = synthetic_sequence(lengths, 52)
+    weights = wl.head_weights(seed=51)
+    for layer in range(2):  # the query and key rows of both layers
+        at = 320 + 33472 * layer
+        weights[at:at + 128 * 64] *= scale
+    offd, wd = torch.tensor(off, device="cuda"), torch.tensor(weights, device="cuda")
+    L = pr._abi.lib()
+    need = int((L.pr_verifier_head_workspace_full if full else L.pr_verifier_head_workspace)(X.shape[0]))
+
+    def run(x, fill):
+        ws = torch.full((need,), fill, dtype=torch.uint8, device="cuda")
+        s = pr.verifier_head(torch.tensor(x, device="cuda"), offd, wd, max_len=333, workspace=ws)
+        torch.cuda.synchronize()
+        return s.cpu().numpy()
+
+    print(f"case head alone scale={scale} full={full} rows={X.shape[0]}", flush=True)
+    want = run(X, 0)
+    assert_floats("head score", want, ohead.head_scores(X.astype(np.float64), off, weights.astype(np.float64)))
+    for fill in (0, 0x7F, 0xFF):  # zeros, the largest finite values, NaN in every type
+        assert np.array_equal(run(X, fill).view(np.uint32), want.view(np.uint32)), fill
+    for keep in (0, 1):  # every second request stays, its neighbours change
+        x = other.copy()
+        for i in range(keep, len(lengths), 2):
+            x[off[i]:off[i + 1]] = X[off[i]:off[i + 1]]
+        got = run(x, 0xFF)
+        assert np.array_equal(got[keep::2].view(np.uint32), want[keep::2].view(np.uint32)), keep
