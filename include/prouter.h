@@ -388,9 +388,7 @@ typedef struct pr_stream pr_stream;
  * Chlamtac, CACM 1985), 224 bytes per slot, any number of tokens per
  * request. Its estimate is exact up to 5 tokens; an infinite value of a
  * column (a margin of +inf, a log-prob of -inf) makes that column's
- * quantile NaN for the request (the mean and minimum keep it). Besides the
- * slots' state it holds 297 KB per slot, for at most 64 slots, in which top-p
- * steps spread few rows over the device.
+ * quantile NaN for the request (the mean and minimum keep it).
  */
 pr_status pr_stream_create(int32_t max_slots, int32_t max_len, const pr_agg_params* params, pr_stream** state);
 
@@ -406,11 +404,29 @@ pr_status pr_stream_create(int32_t max_slots, int32_t max_len, const pr_agg_para
  * top_p (device float [n_active]) or NULL: with it, the features and the
  * tuple A that joins the slot are those of the renormalised nucleus, as in
  * pr_token_features (vocab below 2^24, PR_ERR_UNSUPPORTED otherwise).
+ * Steps with top_p use no scratch of the state: those on disjoint slots may
+ * overlap (other streams or host threads). Steps without it may keep split
+ * rows' partial states there: they must be ordered among themselves.
  */
 pr_status pr_stream_step(pr_stream* state, const void* logits, pr_dtype dtype, int32_t n_active,
                          int32_t vocab, int64_t row_stride, const int32_t* slot_ids,
                          const int32_t* sampled_ids, const float* temperature, const float* top_p,
                          const pr_token_features_t* out, void* stream);
+
+/*
+ * pr_stream_step with a workspace, with which top-p steps of few rows spread
+ * each row over several workgroups; whole numbers are the same, floats to
+ * float32 rounding. The first function gives the bytes it can use for a step
+ * (0: none); with a smaller or NULL workspace the call is pr_stream_step.
+ *   workspace  device scratch, 16-byte aligned, not shared with a call that
+ *              may overlap; no initialisation needed.
+ */
+size_t pr_stream_step_workspace(pr_dtype dtype, int32_t n_active, int32_t vocab, int32_t top_p_on);
+pr_status pr_stream_step_ws(pr_stream* state, const void* logits, pr_dtype dtype, int32_t n_active,
+                            int32_t vocab, int64_t row_stride, const int32_t* slot_ids,
+                            const int32_t* sampled_ids, const float* temperature, const float* top_p,
+                            const pr_token_features_t* out, void* workspace, size_t workspace_bytes,
+                            void* stream);
 
 /*
  * Finishes n requests: for each slots[i] (device int32 [n]) computes the

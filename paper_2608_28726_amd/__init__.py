@@ -400,9 +400,13 @@ class StreamState:
         elif out is not None:
             _check_features(out, logits.device, n, "out")
         fs = C.byref(_features_struct(out)) if out is not None else None
-        st = _abi.lib().pr_stream_step(self._h, _ptr(logits), _dtype_code(logits), n, V, logits.stride(0),
-                                       _ptr(slot_ids), _ptr(sampled_ids), _ptr(temperature), _ptr(top_p), fs,
-                                       _stream_handle())
+        L = _abi.lib()
+        code = _dtype_code(logits)
+        need = L.pr_stream_step_workspace(code, n, V, 1) if top_p is not None else 0
+        ws = torch.empty(need, dtype=torch.uint8, device=logits.device) if need else None
+        st = L.pr_stream_step_ws(self._h, _ptr(logits), code, n, V, logits.stride(0), _ptr(slot_ids),
+                                 _ptr(sampled_ids), _ptr(temperature), _ptr(top_p), fs, _ptr(ws), need,
+                                 _stream_handle())
         _abi.check("pr_stream_step", st)
         return out
 

@@ -29,7 +29,7 @@ EXPORTED = (
     "pr_calibrate_workspace", "pr_sample_features", "pr_token_features_noalloc",
     "pr_feature_sequence_workspace", "pr_feature_sequence_ws", "pr_sample_features_workspace",
     "pr_sample_features_ws", "pr_verifier_head_workspace_full",
-    "pr_token_features_workspace_full",
+    "pr_token_features_workspace_full", "pr_stream_step_workspace", "pr_stream_step_ws",
 )
 
 PR_HEAD_WEIGHTS = 67329
@@ -118,6 +118,11 @@ def lib() -> C.CDLL:
     L.pr_stream_create.restype = C.c_int
     L.pr_stream_step.argtypes = [vp, vp, C.c_int, i32, i32, i64, vp, vp, vp, vp, C.POINTER(TokenFeatures), vp]
     L.pr_stream_step.restype = C.c_int
+    L.pr_stream_step_workspace.argtypes = [C.c_int, i32, i32, i32]
+    L.pr_stream_step_workspace.restype = sz
+    L.pr_stream_step_ws.argtypes = [vp, vp, C.c_int, i32, i32, i64, vp, vp, vp, vp, C.POINTER(TokenFeatures), vp, sz,
+                                    vp]
+    L.pr_stream_step_ws.restype = C.c_int
     L.pr_stream_finish.argtypes = [vp, vp, i32, f32, C.POINTER(RequestAgg), vp, vp]
     L.pr_stream_finish.restype = C.c_int
     L.pr_stream_reset_slots.argtypes = [vp, vp, i32, vp]

@@ -23,8 +23,6 @@ struct pr_stream {
   StreamDev dev;
   pr_agg_params params;
   Partial* ws;  // split-row workspace for up to max_slots rows of kStreamMaxSplit workgroups
-  void* tws;    // the same for top-p steps of few rows
-  size_t tws_bytes;
   void* block;  // single allocation backing everything above
 };
 
@@ -385,8 +383,7 @@ pr_status pr_stream_create(int32_t max_slots, int32_t max_len, const pr_agg_para
   const bool bounded = max_len == 0;  // P-square markers instead of the history
   const size_t b_p2q = bounded ? up(S * 20 * sizeof(double)) : 0;
   const size_t b_p2n = bounded ? up(S * 16 * sizeof(int32_t)) : 0;
-  const size_t b_tws = up(topp_split_workspace_most(static_cast<int64_t>(S)));
-  const size_t total = b_ws + b_sum + b_hist + b_min + b_cnt + b_nan + b_p2q + b_p2n + b_tws;
+  const size_t total = b_ws + b_sum + b_hist + b_min + b_cnt + b_nan + b_p2q + b_p2n;
   pr_stream* s = new (std::nothrow) pr_stream();
   if (!s) return PR_ERR_NO_MEMORY;
   hipError_t e = hipGetDevice(&s->device);
@@ -411,9 +408,6 @@ pr_status pr_stream_create(int32_t max_slots, int32_t max_len, const pr_agg_para
   s->dev.p2q = bounded ? reinterpret_cast<double*>(b) : nullptr;
   b += b_p2q;
   s->dev.p2n = bounded ? reinterpret_cast<int32_t*>(b) : nullptr;
-  b += b_p2n;
-  s->tws = b;
-  s->tws_bytes = b_tws;
   s->dev.p2p = p.q;
   if (bounded) s->dev.hist = nullptr;
   s->dev.max_slots = max_slots;
@@ -430,10 +424,22 @@ pr_status pr_stream_create(int32_t max_slots, int32_t max_len, const pr_agg_para
   return PR_OK;
 }
 
+size_t pr_stream_step_workspace(pr_dtype, int32_t n_active, int32_t vocab, int32_t top_p_on) {
+  return top_p_on ? topp_split_workspace(n_active, vocab) : 0;
+}
+
 pr_status pr_stream_step(pr_stream* state, const void* logits, pr_dtype dtype, int32_t n_active, int32_t vocab,
                          int64_t row_stride, const int32_t* slot_ids, const int32_t* sampled_ids,
                          const float* temperature, const float* top_p, const pr_token_features_t* out,
                          void* stream) {
+  return pr_stream_step_ws(state, logits, dtype, n_active, vocab, row_stride, slot_ids, sampled_ids, temperature,
+                           top_p, out, nullptr, 0, stream);
+}
+
+pr_status pr_stream_step_ws(pr_stream* state, const void* logits, pr_dtype dtype, int32_t n_active, int32_t vocab,
+                            int64_t row_stride, const int32_t* slot_ids, const int32_t* sampled_ids,
+                            const float* temperature, const float* top_p, const pr_token_features_t* out,
+                            void* workspace, size_t workspace_bytes, void* stream) {
   if (!state) return PR_ERR_INVALID_ARG;
   pr_status st = check_rows(logits, dtype, n_active, vocab, row_stride, sampled_ids, temperature);
   if (st != PR_OK) return st;
@@ -441,6 +447,7 @@ pr_status pr_stream_step(pr_stream* state, const void* logits, pr_dtype dtype, i
   if (n_active > 0 && !slot_ids) return PR_ERR_INVALID_ARG;
   if (top_p && vocab >= kTopPMaxVocab) return PR_ERR_UNSUPPORTED;
   if (out && !features_complete(out)) return PR_ERR_INVALID_ARG;
+  if (workspace && !aligned(workspace, 16)) return PR_ERR_INVALID_ARG;
   if (n_active == 0) return PR_OK;
   RowArgs a{};
   a.logits = logits;
@@ -457,7 +464,7 @@ pr_status pr_stream_step(pr_stream* state, const void* logits, pr_dtype dtype, i
   a.ws = state->ws;
   a.slot_ids = slot_ids;
   a.st = state->dev;
-  if (top_p) return hip_status(launch_topp(a, dtype, state->tws, state->tws_bytes, as_stream(stream)));
+  if (top_p) return hip_status(launch_topp(a, dtype, workspace, workspace_bytes, as_stream(stream)));
   return hip_status(launch_row_features(a, dtype, as_stream(stream)));
 }
 

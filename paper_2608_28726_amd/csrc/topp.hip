@@ -49,7 +49,6 @@
 // boundary value) that resolves ties by counting.
 #include "topp.h"
 
-#include <limits>
 #include <type_traits>
 
 #include "p2.h"
@@ -1951,11 +1950,6 @@ __global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) v
 size_t topp_split_workspace(int64_t n_rows, int32_t V) {
   const int64_t most = V >= 131072 ? 128 : (V >= 65536 ? 32 : 0);
   return n_rows > 0 && n_rows <= most ? static_cast<size_t>(n_rows) * sizeof(TpRowWs) : 0;
-}
-
-// (A streaming state keeps room for steps of up to 64 rows, 19 MB.)
-size_t topp_split_workspace_most(int64_t n_rows) {
-  return topp_split_workspace(n_rows < 64 ? n_rows : 64, std::numeric_limits<int32_t>::max());
 }
 
 template <typename Tin, bool SEQ>

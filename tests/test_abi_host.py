@@ -102,6 +102,8 @@ def test_other_entry_points_reject_bad_arguments():
     assert lib.pr_stream_create(4, -1, None, C.byref(h)) == _abi.PR_ERR_INVALID_ARG  # 0 = bounded memory
     assert lib.pr_stream_step(None, None, 1, 0, 100, 100, None, None, None, None, None, None) == \
         _abi.PR_ERR_INVALID_ARG
+    assert lib.pr_stream_step_ws(None, None, 1, 0, 100, 100, None, None, None, None, None, None, 0, None) == \
+        _abi.PR_ERR_INVALID_ARG
     assert lib.pr_stream_finish(None, None, 1, 0.5, None, None, None) == _abi.PR_ERR_INVALID_ARG
     lib.pr_stream_destroy(None)  # ignored
     # zero rows: valid, nothing launched

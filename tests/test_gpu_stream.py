@@ -1,6 +1,9 @@
 """Streaming decode: per-step features, device-resident request state and
 finish-time verdicts equal the offline path and the oracle."""
 
+import ctypes as C
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -173,3 +176,106 @@ def test_stream_with_top_p_bounded_memory():
             e = np.float32(oracle.p2_quantile([np.float32(a[c]) for a in A[i]], 0.3))
             got = results[i]["quant"][c]
             assert got == e or (np.isnan(e) and np.isnan(got)), (i, c, got, e)
+
+
+def _topp_steps(n, V, steps, seed):
+    """Steps of n rows with top-p: (logits, ids, T, P) each, V bfloat16 logits a row."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    out = []
+    for _ in range(steps):
+        z = (torch.randn((n, V), generator=g, device="cuda") * 2.5).to(torch.bfloat16)
+        out.append((z, torch.argmax(z.float(), 1).to(torch.int32), torch.full((n,), 0.8, device="cuda"),
+                    torch.full((n,), 0.9, device="cuda")))
+    torch.cuda.synchronize()
+    return out
+
+
+def test_top_p_steps_of_one_state_may_overlap():
+    """Top-p steps on disjoint slots of one state, from two threads with a
+    stream each: the features and verdicts of the same steps in order."""
+    n, steps = 16, 12
+    data = [_topp_steps(n, 151936, steps, 61 + k) for k in range(2)]
+    slots = [torch.arange(k * n, (k + 1) * n, dtype=torch.int32, device="cuda") for k in range(2)]
+    print("case stream top-p steps from two threads", flush=True)
+
+    def feed(state, k, stream, out):
+        with torch.cuda.stream(stream):
+            out[k] = [state.step(z, slots[k], ids, T, want_features=True, top_p=P) for z, ids, T, P in data[k]]
+
+    results = []
+    for overlap in (False, True):
+        st = pr.StreamState(2 * n, steps)
+        feats = [None, None]
+        if overlap:
+            streams = [torch.cuda.Stream() for _ in range(2)]
+            work = [threading.Thread(target=feed, args=(st, k, streams[k], feats)) for k in range(2)]
+            for w in work:
+                w.start()
+            for w in work:
+                w.join()
+        else:
+            for k in range(2):
+                feed(st, k, torch.cuda.current_stream(), feats)
+        torch.cuda.synchronize()
+        res = st.finish(torch.cat(slots), 0.5)
+        torch.cuda.synchronize()
+        st.close()
+        results.append((feats, res))
+    (fa, ra), (fb, rb) = results
+    for k in range(2):
+        for a, b in zip(fa[k], fb[k]):
+            for key in a:
+                assert torch.equal(a[key].view(torch.int32), b[key].view(torch.int32)), (k, key)
+    assert int(ra["count"].min()) == steps
+    for key in ra:
+        assert torch.equal(ra[key], rb[key]), key
+
+
+def test_top_p_step_with_and_without_workspace():
+    """The C entry points: a step with the workspace it asks for writes nothing
+    past it, and agrees with a step that has none or too little."""
+    L = pr._abi.lib()
+    n, V = 5, 70001
+    slots = torch.arange(n, dtype=torch.int32, device="cuda")
+    z, ids, T, P = _topp_steps(n, V, 1, 63)[0]
+    need = int(L.pr_stream_step_workspace(pr._abi.PR_BF16, n, V, 1))
+    assert need > 0 and L.pr_stream_step_workspace(pr._abi.PR_BF16, n, V, 0) == 0
+    buf = torch.full((need + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+    got = []
+    for size in (need, 0, need - 16):
+        st = pr.StreamState(n, 4)
+        f = pr._alloc_features(n, z.device)
+        args = (st._h, z.data_ptr(), pr._abi.PR_BF16, n, V, V, slots.data_ptr(), ids.data_ptr(), T.data_ptr(),
+                P.data_ptr(), C.byref(pr._features_struct(f)))
+        if size:
+            if size < need:
+                buf.fill_(0xFF)
+            s = L.pr_stream_step_ws(*args, buf.data_ptr(), size, pr._stream_handle())
+        else:
+            s = L.pr_stream_step(*args, pr._stream_handle())
+        assert s == 0
+        torch.cuda.synchronize()
+        assert bool((buf[need if size == need else 0:] == 0xFF).all()) or not size
+        got.append((f, st.finish(slots, 0.5)))
+        torch.cuda.synchronize()
+        assert L.pr_stream_step_ws(*args, buf.data_ptr() + 8, need, pr._stream_handle()) == pr._abi.PR_ERR_INVALID_ARG
+        st.close()
+    compare_features({k: v.cpu().numpy() for k, v in got[0][0].items()}, oracle_features(z, ids, T, P))
+    for f, r in got[1:]:
+        for k in f:
+            if f[k].dtype == torch.int32:
+                assert torch.equal(f[k], got[0][0][k]), k
+            else:
+                assert_floats(k, f[k].cpu().numpy(), got[0][0][k].cpu().numpy(), rtol=1e-6, atol=1e-6)
+        assert torch.equal(r["count"], got[0][1]["count"])
+
+
+def test_a_state_holds_its_slots_alone():
+    """No scratch of a state grows with what steps may want: 64 bounded-memory
+    slots take under 4 MB of the device."""
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    st = pr.StreamState(64, 0)
+    after = torch.cuda.mem_get_info()[0]
+    st.close()
+    assert before - after < 4 << 20
