@@ -131,9 +131,6 @@ void pr_agg_params_default(pr_agg_params* params);
  * none). top_p_on: 1 if a top-p array will be passed.
  */
 size_t pr_token_features_workspace(pr_dtype dtype, int64_t n_rows, int32_t vocab, int32_t top_p_on);
-/* The bytes with which small batches run fastest (top-p rows are then spread
- * over several workgroups each); at least pr_token_features_workspace. */
-size_t pr_token_features_workspace_full(pr_dtype dtype, int64_t n_rows, int32_t vocab, int32_t top_p_on);
 
 /*
  * Per-token features of n_rows logit rows (Sec. 3.1, Eq. 3, extended to the
@@ -152,13 +149,29 @@ size_t pr_token_features_workspace_full(pr_dtype dtype, int64_t n_rows, int32_t 
  *                required.
  *   workspace    device scratch of at least
  *                pr_token_features_workspace(...) bytes (may be NULL when that
- *                is 0). Its contents need no initialisation.
+ *                is 0). Its contents need no initialisation. Not used with
+ *                top_p.
  * n_rows == 0 is valid and launches nothing.
  */
 pr_status pr_token_features(const void* logits, pr_dtype dtype, int64_t n_rows, int32_t vocab,
                             int64_t row_stride, const int32_t* sampled_ids, const float* temperature,
                             const float* top_p, const pr_token_features_t* out, void* workspace,
                             size_t workspace_bytes, void* stream);
+
+/*
+ * pr_token_features that with top_p uses a workspace too, with which small
+ * batches spread each row over several workgroups; whole numbers are the same,
+ * floats to float32 rounding. The first function gives the bytes it can use
+ * for a shape (at least pr_token_features_workspace; with top_p, 0: none); with
+ * top_p and a smaller or NULL workspace the call is pr_token_features.
+ *   workspace  device scratch, 16-byte aligned, not shared with a call that
+ *              may overlap; no initialisation needed.
+ */
+size_t pr_token_features_workspace_full(pr_dtype dtype, int64_t n_rows, int32_t vocab, int32_t top_p_on);
+pr_status pr_token_features_ws(const void* logits, pr_dtype dtype, int64_t n_rows, int32_t vocab,
+                               int64_t row_stride, const int32_t* sampled_ids, const float* temperature,
+                               const float* top_p, const pr_token_features_t* out, void* workspace,
+                               size_t workspace_bytes, void* stream);
 
 /*
  * pr_token_features for callers that cannot allocate device memory (code

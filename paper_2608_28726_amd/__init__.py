@@ -129,6 +129,8 @@ def token_features(logits: torch.Tensor, sampled_ids: torch.Tensor, temperature,
     ``logits`` [n_rows, V] float32/bfloat16; ``sampled_ids`` int32 [n_rows];
     ``temperature`` float32 [n_rows] or a Python float; ``top_p`` float32
     [n_rows], a Python float or None. Returns a dict of [n_rows] tensors.
+    ``workspace``: optional device scratch of this call, not shared with one
+    that may overlap (by default as much as the call can use is allocated).
     """
     n, V = logits.shape
     temperature = _as_row_tensor(temperature, n, logits.device)
@@ -146,10 +148,12 @@ def token_features(logits: torch.Tensor, sampled_ids: torch.Tensor, temperature,
                              < L.pr_token_features_workspace(code, n, V, top_p_on)):
         full = L.pr_token_features_workspace_full(code, n, V, top_p_on)
         workspace = torch.empty(full, dtype=torch.uint8, device=logits.device) if full else None
+    elif top_p_on and workspace.data_ptr() % 16:
+        workspace = None  # none is needed
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = L.pr_token_features(_ptr(logits), code, n, V, logits.stride(0), _ptr(sampled_ids), _ptr(temperature),
-                             _ptr(top_p), C.byref(_features_struct(out)), _ptr(workspace), ws_bytes,
-                             _stream_handle())
+    st = L.pr_token_features_ws(_ptr(logits), code, n, V, logits.stride(0), _ptr(sampled_ids), _ptr(temperature),
+                                _ptr(top_p), C.byref(_features_struct(out)), _ptr(workspace), ws_bytes,
+                                _stream_handle())
     _abi.check("pr_token_features", st)
     return out
 

@@ -29,7 +29,7 @@ EXPORTED = (
     "pr_calibrate_workspace", "pr_sample_features", "pr_token_features_noalloc",
     "pr_feature_sequence_workspace", "pr_feature_sequence_ws", "pr_sample_features_workspace",
     "pr_sample_features_ws", "pr_verifier_head_workspace_full",
-    "pr_token_features_workspace_full", "pr_stream_step_workspace", "pr_stream_step_ws",
+    "pr_token_features_workspace_full", "pr_stream_step_workspace", "pr_stream_step_ws", "pr_token_features_ws",
 )
 
 PR_HEAD_WEIGHTS = 67329
@@ -79,6 +79,8 @@ def lib() -> C.CDLL:
     L.pr_token_features_workspace_full.restype = sz
     L.pr_token_features.argtypes = [vp, C.c_int, i64, i32, i64, vp, vp, vp, C.POINTER(TokenFeatures), vp, sz, vp]
     L.pr_token_features.restype = C.c_int
+    L.pr_token_features_ws.argtypes = L.pr_token_features.argtypes
+    L.pr_token_features_ws.restype = C.c_int
     L.pr_token_features_noalloc.argtypes = [vp, C.c_int, i64, i32, i64, vp, vp, vp, C.POINTER(TokenFeatures), vp]
     L.pr_token_features_noalloc.restype = C.c_int
     L.pr_feature_sequence.argtypes = [vp, C.c_int, i64, i32, i64, vp, vp, vp, vp, i32, i32, vp,

@@ -146,11 +146,20 @@ pr_status pr_token_features(const void* logits, pr_dtype dtype, int64_t n_rows, 
                             int64_t row_stride, const int32_t* sampled_ids, const float* temperature,
                             const float* top_p, const pr_token_features_t* out, void* workspace,
                             size_t workspace_bytes, void* stream) {
+  return pr_token_features_ws(logits, dtype, n_rows, vocab, row_stride, sampled_ids, temperature, top_p, out,
+                              top_p ? nullptr : workspace, top_p ? 0 : workspace_bytes, stream);
+}
+
+pr_status pr_token_features_ws(const void* logits, pr_dtype dtype, int64_t n_rows, int32_t vocab,
+                               int64_t row_stride, const int32_t* sampled_ids, const float* temperature,
+                               const float* top_p, const pr_token_features_t* out, void* workspace,
+                               size_t workspace_bytes, void* stream) {
   pr_status st = check_rows(logits, dtype, n_rows, vocab, row_stride, sampled_ids, temperature);
   if (st != PR_OK) return st;
   if (!features_complete(out)) return PR_ERR_INVALID_ARG;
   const size_t need = pr_token_features_workspace(dtype, n_rows, vocab, top_p ? 1 : 0);
   if (need > 0 && (!workspace || workspace_bytes < need || !aligned(workspace, 16))) return PR_ERR_INVALID_ARG;
+  if (top_p && workspace && !aligned(workspace, 16)) return PR_ERR_INVALID_ARG;
   if (n_rows == 0) return PR_OK;
   RowArgs a{};
   a.logits = logits;
@@ -162,10 +171,7 @@ pr_status pr_token_features(const void* logits, pr_dtype dtype, int64_t n_rows, 
   a.top_p = top_p;
   a.out = *out;
   if (top_p && vocab >= kTopPMaxVocab) return PR_ERR_UNSUPPORTED;
-  if (top_p) {
-    if (!aligned(workspace, 16)) workspace = nullptr;
-    return hip_status(launch_topp(a, dtype, workspace, workspace_bytes, as_stream(stream)));
-  }
+  if (top_p) return hip_status(launch_topp(a, dtype, workspace, workspace_bytes, as_stream(stream)));
   a.G = row_split(n_rows, vocab, dtype);
   a.ws = static_cast<Partial*>(workspace);
   return hip_status(launch_row_features(a, dtype, as_stream(stream)));

@@ -1,6 +1,7 @@
 """Top-p (nucleus) features: exact cutoff index, rank and renormalised
 features, HIP path vs the fp64 oracle."""
 
+import ctypes as C
 import math
 
 import numpy as np
@@ -370,3 +371,39 @@ def test_topp_row_and_vocabulary_limits():
         rows = [0, n - 1]
         o = oracle_features(z, ids, T, P, rows)
         compare_features({k: v.cpu().numpy() for k, v in f.items()}, o, rows)
+
+
+def test_token_features_leaves_the_workspace_alone_with_top_p():
+    """pr_token_features asks for no workspace with top-p and does not touch one
+    that it is given, whatever its alignment (a caller may pass one buffer to
+    calls that overlap); pr_token_features_ws uses it, wants it aligned, and
+    does without it when it is too small."""
+    L = pr._abi.lib()
+    n, V = 4, 70001
+    g = torch.Generator(device="cuda").manual_seed(5)
+    z = torch.randn((n, V), generator=g, device="cuda") * 2.5
+    ids = torch.argmax(z, 1).to(torch.int32)
+    T, P = torch.full((n,), 0.8, device="cuda"), torch.full((n,), 0.9, device="cuda")
+    full = int(L.pr_token_features_workspace_full(pr._abi.PR_F32, n, V, 1))
+    assert full > 0 and L.pr_token_features_workspace(pr._abi.PR_F32, n, V, 1) == 0
+    buf = torch.full((full + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+    ref = oracle_features(z, ids, T, P)
+
+    def call(fn, shift, size):
+        f = pr._alloc_features(n, z.device)
+        st = fn(z.data_ptr(), pr._abi.PR_F32, n, V, V, ids.data_ptr(), T.data_ptr(), P.data_ptr(),
+                C.byref(pr._features_struct(f)), buf.data_ptr() + shift, size, pr._stream_handle())
+        torch.cuda.synchronize()
+        if st == 0:
+            compare_features({k: v.cpu().numpy() for k, v in f.items()}, ref)
+        return st, bool((buf == 0xFF).all())
+
+    print("case topp and the given workspace", flush=True)
+    assert call(L.pr_token_features, 0, full) == (0, True)
+    assert call(L.pr_token_features, 8, full) == (0, True)
+    assert call(L.pr_token_features_ws, 0, full - 16) == (0, True)
+    assert call(L.pr_token_features_ws, 8, full) == (pr._abi.PR_ERR_INVALID_ARG, True)
+    assert call(L.pr_token_features_ws, 0, full) == (0, False)
+    assert bool((buf[full:] == 0xFF).all())
+    out = pr.token_features(z, ids, T, P, workspace=buf[8:])  # the binding does without a misaligned one
+    compare_features({k: v.cpu().numpy() for k, v in out.items()}, ref)
