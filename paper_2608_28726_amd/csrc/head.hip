@@ -605,7 +605,8 @@ __device__ __forceinline__ void layer_norm(f4& x, const f4& g, const f4& b) {
   for (int e = 0; e < 4; ++e) x[e] = fmaf(x[e] * inv, g[e], b[e]);
 }
 
-// One encoder layer of one block (see the top of the file). LAST: the rows'
+// One encoder layer of one block (see the top of the file), block `from` of
+// the list and those after it. LAST: the rows'
 // products with the output map instead of the next layer's projections.
 // Eight waves: in the attention wave w is head w % 4 over half w / 4 of the
 // key tiles; of the dense products waves 0-3 make those with 64 columns, 16
@@ -614,7 +615,7 @@ __device__ __forceinline__ void layer_norm(f4& x, const f4& g, const f4& b) {
 // took 143, one workgroup per CU, and 104 instead of 86 us on 64 requests of
 // 16 to 512 tokens).
 template <bool LAST>
-__global__ __launch_bounds__(kThreads) void head_layer_kernel(HeadArgs a, int layer) {
+__global__ __launch_bounds__(kThreads) void head_layer_kernel(HeadArgs a, int layer, int32_t from) {
   constexpr int kPA = kRows * kBA, kPF = kRows * kBF;  // planes of split activations
   __shared__ __attribute__((aligned(16))) __bf16 sB[3 * kPA];     // attention output, then h1, then h2, split
   __shared__ __attribute__((aligned(16))) float sY[kRows * kSA];  // y, then h1, then z
@@ -626,8 +627,9 @@ __global__ __launch_bounds__(kThreads) void head_layer_kernel(HeadArgs a, int la
     } at;
   } su;
   const int32_t count = a.ctl[0];
-  const HeadBlock it = a.items[blockIdx.x];
-  if (static_cast<int32_t>(blockIdx.x) >= count) return;
+  const int32_t block = from + static_cast<int32_t>(blockIdx.x);
+  const HeadBlock it = a.items[block];
+  if (block >= count) return;
   const int64_t r0 = it.r0, lo = it.lo, hi = it.hi;
   const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
   const int i16 = lane % 16, g = lane / 16;
@@ -822,11 +824,21 @@ hipError_t launch_head(const HeadArgs& args, hipStream_t stream) {
     const int64_t tiles = (a.n_rows + kRows - 1) / kRows;
     // at most this many blocks: a request of T rows has at most (T + 3) / 16 + 1, and at most T
     const int64_t most = (a.n_rows + 3 * static_cast<int64_t>(a.n_req)) / kRows + a.n_req;
-    const unsigned grid = static_cast<unsigned>(most < a.n_rows ? most : a.n_rows);
+    const int64_t blocks = most < a.n_rows ? most : a.n_rows;
+    // A launch holds fewer than 2^32 threads (more are cut off without an
+    // error), so a longer list takes several.
+    constexpr int64_t kMaxBlocks = (int64_t{1} << 32) / kThreads - 1;
+    auto each_launch = [&](auto&& launch) {
+      for (int64_t from = 0; from < blocks; from += kMaxBlocks)
+        launch(static_cast<unsigned>(blocks - from < kMaxBlocks ? blocks - from : kMaxBlocks), static_cast<int32_t>(from));
+    };
     head_embed_kernel<<<static_cast<unsigned>((tiles < kEmbedWgs ? tiles : kEmbedWgs) + 1 + kSplitWgs), kThreads, 0,
                         stream>>>(a);
-    for (int l = 0; l + 1 < kHeadLayers; ++l) head_layer_kernel<false><<<grid, kThreads, 0, stream>>>(a, l);
-    head_layer_kernel<true><<<grid, kThreads, 0, stream>>>(a, kHeadLayers - 1);
+    for (int l = 0; l + 1 < kHeadLayers; ++l)
+      each_launch([&](unsigned n, int32_t from) { head_layer_kernel<false><<<n, kThreads, 0, stream>>>(a, l, from); });
+    each_launch([&](unsigned n, int32_t from) {
+      head_layer_kernel<true><<<n, kThreads, 0, stream>>>(a, kHeadLayers - 1, from);
+    });
   }
   head_score_kernel<<<static_cast<unsigned>(a.n_req), kWave, 0, stream>>>(a);
   return hipGetLastError();

@@ -219,3 +219,22 @@ def test_score_depends_on_its_request_alone(scale, full):
             x[off[i]:off[i + 1]] = X[off[i]:off[i + 1]]
         got = run(x, 0xFF)
         assert np.array_equal(got[keep::2].view(np.uint32), want[keep::2].view(np.uint32)), keep
+
+
+def test_more_row_blocks_than_one_launch_holds():
+    """8.4 million requests of one token, each a block of the layer kernel: more
+    threads than one launch may have. Their scores are those of the same
+    tokens in a small batch."""
+    n, few = (1 << 23) + 5003, 4096
+    if torch.cuda.mem_get_info()[0] < 40 << 30:
+        pytest.skip("needs 20 GB of device memory")
+    X, _ = synthetic_sequence([1] * few, 71)
+    weights = wl.head_weights(seed=71)
+    want = run_head(X, np.arange(few + 1, dtype=np.int32), weights, max_len=1)
+    print(f"case head {n} requests", flush=True)
+    Xd = torch.tensor(X, device="cuda").repeat((n + few - 1) // few, 1)[:n].contiguous()
+    got = pr.verifier_head(Xd, torch.arange(n + 1, dtype=torch.int32, device="cuda"),
+                           torch.tensor(weights, device="cuda"), max_len=1)
+    torch.cuda.synchronize()
+    got = got.cpu().numpy()
+    assert np.array_equal(got.view(np.uint32), np.resize(want, n).view(np.uint32))
