@@ -407,3 +407,34 @@ def test_token_features_leaves_the_workspace_alone_with_top_p():
     assert bool((buf[full:] == 0xFF).all())
     out = pr.token_features(z, ids, T, P, workspace=buf[8:])  # the binding does without a misaligned one
     compare_features({k: v.cpu().numpy() for k, v in out.items()}, ref)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_topp_rows_masked_at_their_start(dtype):
+    """Rows whose first 8,000 logits are masked, over several workgroups: what
+    the oracle gives, in about the time of the same rows unmasked (the method
+    for rows without an anchor takes three to five times as long)."""
+    n, V = 16, 262144
+    g = torch.Generator(device="cuda").manual_seed(17)
+    z = (torch.randn((n, V), generator=g, device="cuda") * 2.5).to(dtype)
+    T, P = torch.full((n,), 0.8, device="cuda"), torch.full((n,), 0.9, device="cuda")
+    masked = z.clone()
+    masked[:, :8000] = -math.inf
+    print(f"case topp masked start {dtype}", flush=True)
+    best = []
+    for x in (z, masked):
+        ids = torch.argmax(x.float(), 1).to(torch.int32)
+        f = pr.token_features(x, ids, T, P)
+        rows = [0, n - 1]
+        compare_features({k: v.cpu().numpy() for k, v in f.items()}, oracle_features(x, ids, T, P, rows), rows)
+        times = []
+        for _ in range(20):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                pr.token_features(x, ids, T, P)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        best.append(min(times))
+    assert best[1] < 2.0 * best[0], best
