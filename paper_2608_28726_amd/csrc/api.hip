@@ -139,7 +139,7 @@ size_t pr_token_features_workspace(pr_dtype dtype, int64_t n_rows, int32_t vocab
 
 size_t pr_token_features_workspace_full(pr_dtype dtype, int64_t n_rows, int32_t vocab, int32_t top_p_on) {
   if (n_rows <= 0 || vocab < 2) return 0;
-  return top_p_on ? topp_split_workspace(n_rows, vocab) : pr_token_features_workspace(dtype, n_rows, vocab, 0);
+  return top_p_on ? topp_split_workspace(n_rows, vocab, false) : pr_token_features_workspace(dtype, n_rows, vocab, 0);
 }
 
 pr_status pr_token_features(const void* logits, pr_dtype dtype, int64_t n_rows, int32_t vocab,
@@ -197,7 +197,7 @@ pr_status pr_token_features_noalloc(const void* logits, pr_dtype dtype, int64_t 
 
 size_t pr_feature_sequence_workspace(pr_dtype dtype, int64_t n_rows, int32_t vocab, int32_t top_p_on) {
   if (vocab < 2) return 0;
-  return top_p_on ? topp_split_workspace(n_rows, vocab) : lane_workspace_bytes(n_rows, vocab, dtype, true, false);
+  return top_p_on ? topp_split_workspace(n_rows, vocab, true) : lane_workspace_bytes(n_rows, vocab, dtype, true, false);
 }
 
 pr_status pr_feature_sequence(const void* logits, pr_dtype dtype, int64_t n_rows, int32_t vocab,
@@ -431,7 +431,7 @@ pr_status pr_stream_create(int32_t max_slots, int32_t max_len, const pr_agg_para
 }
 
 size_t pr_stream_step_workspace(pr_dtype, int32_t n_active, int32_t vocab, int32_t top_p_on) {
-  return top_p_on ? topp_split_workspace(n_active, vocab) : 0;
+  return top_p_on ? topp_split_workspace(n_active, vocab, false) : 0;
 }
 
 pr_status pr_stream_step(pr_stream* state, const void* logits, pr_dtype dtype, int32_t n_active, int32_t vocab,

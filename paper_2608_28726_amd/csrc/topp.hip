@@ -1951,18 +1951,39 @@ __global__ __launch_bounds__(kTpBlock) __attribute__((amdgpu_waves_per_eu(4))) v
 }
 
 // The batches whose rows are spread, at the price of three more launches and
-// of 32 KB of histogram written and read per part. One workgroup per row
-// against eight, us: V = 151,936 bf16 1 row 58 / 39, 16 rows 94 / 52, 64 rows
-// 112 / 71, 128 rows 118 / 97, 200 rows 133 / 138; V = 262,144 f32 16 rows 146 /
-// 52, 128 rows 185 / 110; V = 65,536 16 rows 54 / 40 (bf16), 61 / 40 (f32), but
-// 128 rows 62 / 64; V = 50,257 64 rows 47 / 51; V = 32,000 16 rows 36 / 39. The
-// sequence variant: V = 151,936 bf16 1 row 64 / 54, 16 rows 101 / 67, 64 rows
-// 118 / 85, 128 rows 126 / 119; V = 262,144 f32 64 rows 174 / 90, 128 rows 188 /
-// 135; V = 131,072 128 rows 129 / 103 (bf16), 126 / 109 (f32); V = 65,536 32 rows
-// 63 / 55 (bf16), 61 / 58 (f32).
-size_t topp_split_workspace(int64_t n_rows, int32_t V) {
-  const int64_t most = V >= 131072 ? 128 : (V >= 65536 ? 32 : 0);
-  return n_rows > 0 && n_rows <= most ? static_cast<size_t>(n_rows) * sizeof(TpRowWs) : 0;
+// of 32 KB of histogram written and read per part. One workgroup takes 30 us
+// and more for a peaked row and up to four times as long for a flat one, and a
+// batch takes as long as its slowest row; the eight parts' time depends little
+// on the row. So the lines lie by the means over 16 to 20 batches of rows of
+// all kinds (s = 1..4 and a spike of 0..15, T = 0.3..1.2, P = 0.8..0.95), the
+// time with one workgroup over that with eight, bf16 / f32:
+//   features           1 row         4 rows       32 rows      64 rows      128 rows
+//   V = 50,257      1.03 / 1.11   1.17 / 1.22   1.19 / 1.24   1.02 / 0.99  0.86 / 0.86
+//   V = 65,536      1.10 / 1.10   1.28 / 1.26   1.34 / 1.24   1.22 / 1.12  0.98 / 0.95
+//   V = 98,304      1.17 / 1.18   1.31 / 1.28   1.47 / 1.48   1.23 / 1.20  1.01 / 0.99
+//   V = 128,256     1.45 / 1.48   1.57 / 1.75   1.69 / 1.82   1.63 / 1.78  1.27 / 1.21
+//   V = 151,936     1.58 / 1.49   1.73 / 1.46   1.92 / 2.10   1.56 / 1.58  1.21 / 1.14
+//   V = 262,144     1.83 / 1.74   2.34 / 2.28   2.56 / 2.73   2.30 / 2.52  1.64 / 1.64
+//   sequence
+//   V = 65,536      0.92 / 0.90   1.06 / 1.02   1.13 / 1.03   1.06 / 0.95  0.83 / 0.76
+//   V = 98,304      0.98 / 0.96   1.09 / 1.05   1.26 / 1.21   1.08 / 1.03  0.88 / 0.82
+//   V = 114,688     0.90 / 0.88   1.16 / 1.11   1.43 / 1.31   1.32 / 1.14  0.96 / 0.93
+//   V = 128,256     1.16 / 1.17   1.27 / 1.37   1.43 / 1.47   1.41 / 1.45  1.06 / 0.97
+//   V = 151,936     1.30 / 1.21   1.43 / 1.20   1.64 / 1.72   1.38 / 1.35  1.05 / 0.96
+//   V = 200,064     1.51 / 1.49        -             -             -        1.35 / 1.27
+// The lines are the same for both where neither loses, so that a row's
+// features come out the same to the bit, and 1 to 3 rows of less than 128,000
+// logits stay whole: of their batches up to half, the peaked ones, lose. Above 96
+// rows of less than 196,608 the sequence variant loses as often as it gains (96
+// rows: 1.13 to 1.24 / 1.10 to 1.15); 160 rows are 0.98 / 0.96 for the features at
+// V = 151,936.
+size_t topp_split_workspace(int64_t n_rows, int32_t V, bool seq) {
+  int64_t most = 0;
+  if (V >= 128000) most = seq && V < 196608 ? 96 : 128;
+  else if (V >= 114688) most = 64;
+  else if (V >= 65536) most = 32;
+  const int64_t least = V >= 128000 ? 1 : 4;
+  return n_rows >= least && n_rows <= most ? static_cast<size_t>(n_rows) * sizeof(TpRowWs) : 0;
 }
 
 template <typename Tin, bool SEQ>
@@ -1983,7 +2004,7 @@ hipError_t launch_topp(const RowArgs& args, pr_dtype dtype, void* workspace, siz
   RowArgs a = args;
   const dim3 grid(static_cast<unsigned>(a.n_rows));
   const bool seq = a.X != nullptr;
-  const size_t split = topp_split_workspace(a.n_rows, a.V);
+  const size_t split = topp_split_workspace(a.n_rows, a.V, seq);
   if (split > 0 && workspace && workspace_bytes >= split) {
     a.ws = static_cast<Partial*>(workspace);
     if (dtype == PR_BF16)

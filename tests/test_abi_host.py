@@ -54,6 +54,27 @@ def test_workspace_sizes():
     ws = lib.pr_token_features_workspace(1, 4, 151936, 0)
     assert ws > 0 and ws % 4 == 0 and (ws // 4 - 16) % 32 == 0 and (ws // 4 - 16) // 32 >= 2
     assert lib.pr_token_features_workspace(0, 0, 100, 0) == 0
+    # Top-p rows over several workgroups: a fixed 297 KB per row, where they are spread.
+    row = lib.pr_token_features_workspace_full(1, 1, 151936, 1)
+    assert 290_000 < row < 300_000 and row % 16 == 0
+    full, seq = lib.pr_token_features_workspace_full, lib.pr_feature_sequence_workspace
+    for V, least, most, most_seq in ((65535, 1, 0, 0), (65536, 4, 32, 32), (114687, 4, 32, 32), (114688, 4, 64, 64),
+                                     (127999, 4, 64, 64), (128000, 1, 128, 96), (196607, 1, 128, 96),
+                                     (196608, 1, 128, 128)):
+        for n in (1, 3, 4, 32, 33, 64, 65, 96, 97, 128, 129):
+            assert full(1, n, V, 1) == lib.pr_stream_step_workspace(0, n, V, 1) == (n * row if least <= n <= most else 0)
+            assert seq(0, n, V, 1) == (n * row if least <= n <= most_seq else 0)
+    # Rows over their waves (sequence and sampling without top-p): 16 partial
+    # states and, per lane, 5 words for the sequence and 3 for the draw.
+    assert seq(1, 64, 151936, 0) == 64 * (16 * 32 + 5 * 4096)
+    assert lib.pr_sample_features_workspace(1, 64, 151936, 1) == 64 * (16 * 32 + 8 * 4096)
+    assert lib.pr_sample_features_workspace(1, 64, 151936, 0) == 64 * (16 * 32 + 3 * 4096)
+    assert seq(1, 65, 151936, 0) == 0
+    # The head: the split weights, 1,924 bytes per row padded to whole groups of
+    # 16 and 64 more, a block and its length per row.
+    assert lib.pr_verifier_head_workspace_full(0) == 0
+    for n in (1, 16, 17, 1000):
+        assert lib.pr_verifier_head_workspace_full(n) == 403_584 + ((n + 15) // 16 * 16 + 64) * 1924 + 16 * n + 16
 
 
 @pytest.mark.parametrize("case", ["V<2", "stride<V", "bad dtype", "null logits", "n<0", "null out",

@@ -286,7 +286,8 @@ def test_hardware_exp2_bound():
 
 
 @pytest.mark.parametrize("dtype,V,offset", [(torch.float32, 65536, 0), (torch.float32, 65543, 1),
-                                            (torch.bfloat16, 65536, 0), (torch.bfloat16, 70001, 3)])
+                                            (torch.bfloat16, 65536, 0), (torch.bfloat16, 70001, 3),
+                                            (torch.float32, 98311, 1), (torch.bfloat16, 114699, 3)])
 def test_topp_rows_over_several_workgroups(monkeypatch, dtype, V, offset):
     """Small batches of long rows, each over eight workgroups: every kind of
     row (flat, peaked, ties over the boundary, heavy ties, a distant maximum
@@ -438,3 +439,30 @@ def test_topp_rows_masked_at_their_start(dtype):
             times.append(a.elapsed_time(b))
         best.append(min(times))
     assert best[1] < 2.0 * best[0], best
+
+
+def test_sequence_row_and_vocabulary_limits():
+    """Either side of the batches whose verifier input sequence spreads its
+    rows: X against the oracle."""
+    L = pr._abi.lib()
+    for dtype, n, V, split in ((torch.bfloat16, 32, 65536, True), (torch.bfloat16, 33, 114687, False),
+                               (torch.float32, 3, 127999, False), (torch.float32, 4, 65536, True),
+                               (torch.bfloat16, 1, 128000, True), (torch.bfloat16, 64, 114688, True),
+                               (torch.float32, 96, 131072, True), (torch.float32, 97, 131072, False),
+                               (torch.bfloat16, 8, 65535, False), (torch.bfloat16, 128, 196608, True)):
+        code = pr._abi.PR_BF16 if dtype == torch.bfloat16 else pr._abi.PR_F32
+        assert (L.pr_feature_sequence_workspace(code, n, V, 1) > 0) == split
+        g = torch.Generator(device="cuda").manual_seed(n)
+        z = (torch.randn((n, V), generator=g, device="cuda") * 2.5).to(dtype)
+        ids = torch.argmax(z.float(), 1).to(torch.int32)
+        T, P = torch.full((n,), 0.8, device="cuda"), torch.full((n,), 0.9, device="cuda")
+        off = torch.tensor([0, n], dtype=torch.int32, device="cuda")
+        print(f"case sequence top-p limits n={n} V={V} {dtype}", flush=True)
+        X = pr.feature_sequence(z, ids, T, off, top_p=P)[[0, n - 1]].cpu().numpy()
+        rows = [0, n - 1]
+        o = oracle_features(z, ids, T, P, rows)
+        H = oseq.topk_entropy_batch(wl.to_host_raw(z[rows]), "f32" if dtype == torch.float32 else "bf16",
+                                    T[rows].cpu().numpy(), P[rows].cpu().numpy(), 20)
+        for c, ref in enumerate((o["logprob"], o["maxprob"], H, [1.0 / n, 1.0])):
+            assert_floats(f"X[{c}] n={n} V={V}", X[:, c], -np.asarray(H) if c == 2 else np.asarray(ref, dtype=np.float64),
+                          mask=~o["ambiguous"])
