@@ -1,6 +1,7 @@
 """The paper's verifier head on the GPU (projection + positional encoding,
 two encoder layers, mean pool, sigmoid) vs the fp64 oracle."""
 
+import functools
 import math
 
 import numpy as np
@@ -34,16 +35,29 @@ def synthetic_sequence(lengths, seed):
     return X, off
 
 
-def run_head(X, off, weights, max_len=None):
+def head_workspace(n_rows, full):
+    """Bytes of the documented workspace (the tile kernels), or of the larger one (a kernel per layer)."""
+    L = pr._abi.lib()
+    return int((L.pr_verifier_head_workspace_full if full else L.pr_verifier_head_workspace)(n_rows))
+
+
+def run_head_with(full, X, off, weights, max_len=None):
     Xd = torch.tensor(X, device="cuda").reshape(-1, 4).contiguous()
+    ws = torch.full((head_workspace(Xd.shape[0], full),), 0xFF, dtype=torch.uint8, device="cuda")
     s = pr.verifier_head(Xd, torch.tensor(off, device="cuda"), torch.tensor(weights, device="cuda"),
-                         max_len=max_len)
+                         max_len=max_len, workspace=ws)
     torch.cuda.synchronize()
     return s.cpu().numpy()
 
 
+@pytest.fixture(params=[True, False], ids=["full", "documented"])
+def run_head(request):
+    """The head in a workspace of either size, filled with NaN."""
+    return functools.partial(run_head_with, request.param)
+
+
 @pytest.mark.parametrize("seed", [0, 1])
-def test_ragged_lengths(seed):
+def test_ragged_lengths(seed, run_head):
     """Lengths around every tile and chunk boundary, empty requests included."""
     lengths = [1, 2, 0, 7, 63, 64, 65, 128, 129, 200, 0, 513, 31]
     X, off = synthetic_sequence(lengths, seed)
@@ -55,7 +69,7 @@ def test_ragged_lengths(seed):
     assert np.isnan(got[2]) and np.isnan(got[10])
 
 
-def test_max_len_and_determinism():
+def test_max_len_and_determinism(run_head):
     lengths = [100, 300, 50]
     X, off = synthetic_sequence(lengths, 3)
     weights = wl.head_weights(seed=7)
@@ -66,7 +80,7 @@ def test_max_len_and_determinism():
     assert np.isnan(c[1]) and c[0] == a[0] and c[2] == a[2]
 
 
-def test_many_requests():
+def test_many_requests(run_head):
     """64 requests of U{16..512} tokens, the ragged batch's request shape."""
     rng = np.random.default_rng(11)
     lengths = rng.integers(16, 513, 64).tolist()
@@ -79,7 +93,7 @@ def test_many_requests():
     assert_floats("head score (64 requests)", got[sample], ref)
 
 
-def test_thousands_of_short_requests():
+def test_thousands_of_short_requests(run_head):
     """1,500 requests of 0..40 tokens: more requests than the planning
     workgroup has threads, and a deep search for each row's request; every
     score against the oracle."""
@@ -117,7 +131,7 @@ def test_end_to_end_from_logits():
     assert np.all((ship.cpu().numpy() == expect) | band)
 
 
-def test_work_list_edges():
+def test_work_list_edges(run_head):
     """The attention's work list: no item at all (every request empty or
     longer than max_len), many empty requests around a few real ones, and
     one request of 1,500 tokens (24 key tiles) among short ones; scores
@@ -159,9 +173,8 @@ def test_neighbours_share_row_groups(first, bad, full):
     for i in broken:
         Xb[off[i]:off[i + 1], 0] = bad
     Xd, offd = torch.tensor(Xb, device="cuda"), torch.tensor(off, device="cuda")
-    L = pr._abi.lib()
-    need = int((L.pr_verifier_head_workspace_full if full else L.pr_verifier_head_workspace)(X.shape[0]))
-    buf = torch.full((need + 4096,), 0x7F, dtype=torch.uint8, device="cuda")  # NaN patterns where nothing is written
+    need = head_workspace(X.shape[0], full)
+    buf = torch.full((need + 4096,), 0xFF, dtype=torch.uint8, device="cuda")  # NaN in float32 and in bfloat16
     print(f"case head neighbours first={first} bad={bad} rows={X.shape[0]}", flush=True)
     got = pr.verifier_head(Xd, offd, torch.tensor(weights, device="cuda"), max_len=130, workspace=buf[:need])
     torch.cuda.synchronize()
@@ -169,10 +182,10 @@ def test_neighbours_share_row_groups(first, bad, full):
     ref = ohead.head_scores(X.astype(np.float64), off, weights.astype(np.float64))
     ref[broken] = np.nan
     assert_floats("head score", got, ref)
-    assert bool((buf[need:] == 0x7F).all())
+    assert bool((buf[need:] == 0xFF).all())
 
 
-def test_scaled_weights():
+def test_scaled_weights(run_head):
     """Scores of large magnitude: the softmax reference moves at nearly every
     key tile, and most masses underflow."""
     lengths = [40, 200, 333]
@@ -199,8 +212,7 @@ def test_score_depends_on_its_request_alone(scale, full):
         at = 320 + 33472 * layer
         weights[at:at + 128 * 64] *= scale
     offd, wd = torch.tensor(off, device="cuda"), torch.tensor(weights, device="cuda")
-    L = pr._abi.lib()
-    need = int((L.pr_verifier_head_workspace_full if full else L.pr_verifier_head_workspace)(X.shape[0]))
+    need = head_workspace(X.shape[0], full)
 
     def run(x, fill):
         ws = torch.full((need,), fill, dtype=torch.uint8, device="cuda")
@@ -230,7 +242,7 @@ def test_more_row_blocks_than_one_launch_holds():
         pytest.skip("needs 20 GB of device memory")
     X, _ = synthetic_sequence([1] * few, 71)
     weights = wl.head_weights(seed=71)
-    want = run_head(X, np.arange(few + 1, dtype=np.int32), weights, max_len=1)
+    want = run_head_with(True, X, np.arange(few + 1, dtype=np.int32), weights, max_len=1)
     print(f"case head {n} requests", flush=True)
     Xd = torch.tensor(X, device="cuda").repeat((n + few - 1) // few, 1)[:n].contiguous()
     got = pr.verifier_head(Xd, torch.arange(n + 1, dtype=torch.int32, device="cuda"),
