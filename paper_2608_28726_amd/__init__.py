@@ -278,8 +278,8 @@ def verifier_head(X: torch.Tensor, offsets: torch.Tensor, weights: torch.Tensor,
     :func:`feature_sequence`), ``offsets`` int32 [n_req + 1], ``weights``
     float32 [67,329] in the documented layout. ``max_len``: at least the
     longest request's length (default: n_rows). ``workspace``: optional device
-    scratch of ``pr_verifier_head_workspace_full(n_rows)`` bytes (or, at half
-    the speed, ``pr_verifier_head_workspace(n_rows)``). Returns float32 [n_req]."""
+    scratch of ``pr_verifier_head_workspace_full(n_rows)`` bytes (or, slower,
+    ``pr_verifier_head_workspace(n_rows)``). Returns float32 [n_req]."""
     if X.dtype != torch.float32 or not X.is_cuda or X.dim() != 2 or X.shape[1] != 4 or not X.is_contiguous():
         raise ValueError("X must be a contiguous float32 [n_rows, 4] CUDA tensor")
     if offsets.dtype != torch.int32 or not offsets.is_cuda or offsets.dim() != 1 or not offsets.is_contiguous():
