@@ -295,7 +295,7 @@ pr_status pr_sample_features_ws(const void* logits, pr_dtype dtype, int64_t n_ro
 
 /* The verifier head (Sec. 3.1, the paragraph after Eq. 3; Sec. 4.2): its
  * number of float32 parameters, the device workspace it needs, and the larger
- * one (about 1.3 times that, and 530 KB) with which it runs 1.3 to 4 times as
+ * one (about 1.25 times that, and 527 KB) with which it runs 1.3 to 4 times as
  * fast. */
 #define PR_HEAD_WEIGHTS 67329
 size_t pr_verifier_head_workspace(int64_t n_rows);

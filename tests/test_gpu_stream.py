@@ -279,3 +279,34 @@ def test_a_state_holds_its_slots_alone():
     after = torch.cuda.mem_get_info()[0]
     st.close()
     assert before - after < 4 << 20
+
+
+def test_top_p_step_in_a_captured_graph():
+    """A captured top-p step, replayed on new logits with eager work between
+    the replays: each replay's features are the eager call's to the bit, and
+    the slots gain a token per replay."""
+    n, V = 16, 131072
+    data = _topp_steps(n, V, 3, 67)
+    z, ids, T, P = (t.clone() for t in data[0])
+    slots = torch.arange(n, dtype=torch.int32, device="cuda")
+    st = pr.StreamState(n, 8)
+    st.step(z, slots, ids, T, top_p=P)  # loads the kernels before the capture
+    st.reset(slots)
+    torch.cuda.synchronize()
+    print("case stream top-p step captured", flush=True)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        out = st.step(z, slots, ids, T, want_features=True, top_p=P)
+    for k, (zk, ik, Tk, Pk) in enumerate(data):
+        z.copy_(zk)
+        ids.copy_(ik)
+        g.replay()
+        want = pr.token_features(zk, ik, Tk, Pk)
+        torch.cuda.synchronize()
+        for key in want:
+            assert torch.equal(out[key].view(torch.int32), want[key].view(torch.int32)), (k, key)
+    res = st.finish(slots, 0.5)
+    torch.cuda.synchronize()
+    assert bool((res["count"] == 3).all()) and bool(torch.isfinite(res["quant"]).all())
+    del g
+    st.close()
